@@ -23,8 +23,8 @@
 // order, whatever tile or group its row sits in: rows give the same bits
 // whichever step (and schedule) they are computed in.
 //
-// fp32 path (fp32 stacks): LDS-tiled VALU GEMM, 64x64 tiles, 4x4 per thread,
-// same K-order guarantee.
+// fp32 path (fp32 stacks): the same item walk on fp32 MFMA, 64 x 128 outputs
+// per item, same K-order guarantee.
 #include "eb_internal.h"
 #include "eb_numeric.h"
 
@@ -536,6 +536,46 @@ __device__ __forceinline__ void run_item(const GroupedProblem& p, bf16_t* smem, 
 // it streams 4 activation and 8 weight tiles instead of 32 and 1.
 constexpr int kMBlock = 4;
 
+// A wavefront-uniform value the compiler cannot prove uniform, in scalar
+// registers (buffer descriptors made from vector registers cost a loop per load).
+__device__ __forceinline__ int4 uniform(int4 v) {
+  return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
+                   __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
+}
+
+// Position of an item inside its group's list: column tile and m-tile.
+struct Tile2 {
+  int ni, mi;
+};
+__device__ __forceinline__ Tile2 item_tile(int local, int mt, int n_ntiles) {
+  const int mb = local / (kMBlock * n_ntiles);
+  const int gm = min(kMBlock, mt - mb * kMBlock);
+  const int rb = local - mb * kMBlock * n_ntiles;
+  const int ni = rb / gm;
+  return Tile2{ni, mb * kMBlock + (rb - ni * gm)};
+}
+
+// One thread's view of the item counters: the XCD whose range it draws from.
+struct ItemQueue {
+  int32_t* ctr;
+  long long total;
+  int xcd, victim;
+  __device__ __forceinline__ ItemQueue(const GroupedProblem& p, long long total_)
+      : ctr(p.work_ctr), total(total_), xcd(blockIdx.x % kXcds), victim(blockIdx.x % kXcds) {}
+  __device__ __forceinline__ int range_lo(int x) const { return (int)((x * total) / kXcds); }
+  __device__ __forceinline__ int draw() const { return atomicAdd(&ctr[victim], 1); }
+  // item index from a value drawn from victim's counter, or -1 once every range is drained
+  __device__ __forceinline__ int settle(int got) {
+    int it = range_lo(victim) + got;
+    while (it >= range_lo(victim + 1)) {
+      victim = victim + 1 == kXcds ? 0 : victim + 1;
+      if (victim == xcd) return -1;
+      it = range_lo(victim) + draw();
+    }
+    return it;
+  }
+};
+
 template <int MODE>
 __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem p, WeightTable wt,
                                                                  const bf16_t* __restrict__ A,
@@ -549,33 +589,20 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
   asm volatile("" ::"v"(smem) : "memory");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int xcd = blockIdx.x % kXcds;
   const int ksplit = MODE == MODE_DOWN ? p.ksplit : 1;
   const int nsub = n_ntiles * ksplit;  // items per m-tile
-  const long long total = (long long)(*p.n_tiles) * nsub;
-  auto range_lo = [&](int x) { return (int)((x * total) / kXcds); };
+  ItemQueue q(p, (long long)(*p.n_tiles) * nsub);  // used by thread 0 only
   const int K = MODE == MODE_GATEUP ? p.H : p.F;
   const int ES = p.E + p.S;
 
-  // thread 0: the XCD whose range it draws from, and the first item
-  int victim = xcd;
-  auto settle = [&](int got) {  // item index from a counter value of victim's range, or -1
-    int it = range_lo(victim) + got;
-    while (it >= range_lo(victim + 1)) {
-      victim = victim + 1 == kXcds ? 0 : victim + 1;
-      if (victim == xcd) return -1;
-      it = range_lo(victim) + atomicAdd(&p.work_ctr[victim], 1);
-    }
-    return it;
-  };
-  if (tid == 0) *s_next = settle(atomicAdd(&p.work_ctr[victim], 1));
+  if (tid == 0) *s_next = q.settle(q.draw());
   __syncthreads();
   int it = *s_next;
   __syncthreads();
 
   while (it >= 0) {
     int got = 0;
-    if (tid == 0) got = atomicAdd(&p.work_ctr[victim], 1);
+    if (tid == 0) got = q.draw();
     // group of this item: a group's items it * nsub .. (it + mt) * nsub - 1
     // cover its m-tiles it .. it + mt - 1, so item / nsub is one of them
     const int4 gd = p.tiles[it / nsub];  // key, first row, rows, first m-tile
@@ -584,11 +611,8 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
     // n-tile, m-tile fastest (the last block holds the mt % kMBlock rest)
     const int local = it - gd.w * nsub;
     const int kh = local / (mt * n_ntiles);
-    const int rem = local - kh * mt * n_ntiles;
-    const int mb = rem / (kMBlock * n_ntiles);
-    const int gm = min(kMBlock, mt - mb * kMBlock);
-    const int rb = rem - mb * kMBlock * n_ntiles;
-    const int ni = rb / gm, mi = mb * kMBlock + (rb - ni * gm);
+    const Tile2 tile = item_tile(local - kh * mt * n_ntiles, mt, n_ntiles);
+    const int ni = tile.ni, mi = tile.mi;
     const int nks = K / BK / ksplit, ks0 = kh * nks;
     float* part = ksplit > 1 ? p.partial + (size_t)kh * p.P * p.H : nullptr;
     // the group's mt m-tiles share its rows evenly (whole 32-row blocks), so
@@ -606,7 +630,7 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
       run_item<CfgMid, MODE>(p, smem, A, C, Bbase, row0, row_end, ni, K, ks0, nks, part, wave, lane);
     else
       run_item<CfgSkinny, MODE>(p, smem, A, C, Bbase, row0, row_end, ni, K, ks0, nks, part, wave, lane);
-    if (tid == 0) *s_next = settle(got);
+    if (tid == 0) *s_next = q.settle(got);
     __syncthreads();
     it = *s_next;
     __syncthreads();  // every thread has read it before the next prologue refills the ring
@@ -614,72 +638,186 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
 }
 
 // ---------------------------------------------------------------------------
-// fp32 path
-constexpr int FBM = 64, FBN = 64, FBK = 16;
+// fp32 path: the same grouped, persistent item walk on
+// v_mfma_f32_16x16x4_f32.  An item is 64 rows x 128 weight rows on a workgroup
+// of 8 wavefronts; wavefront w owns weight rows 16 w .. + 15 of the tile
+// (gate/up: 8 gate rows and the matching 8 up rows) for all 64 token rows, so
+// every SIMD works however few rows the item has, and rows are padded to 16
+// only.  K advances 32 per stage (one 128-byte line of each row) through a
+// 3-stage LDS ring filled by buffer loads straight into LDS; 72 KB of LDS, so
+// two workgroups share a CU and cover each other's waits.
+//
+// Bound by the fp32 matrix rate on large groups and by streaming the weights
+// on small ones; a launch takes about the sum of the two.  Measured, H = 1024,
+// F = 2816: one 4096-row group 111 (gate/up) and 95 TFLOP/s (down); 42 groups
+// of one or two rows 5.5 TB/s of weights; a two-layer step of 34 groups and
+// 2400 rows 1125 -> 530 us against the 64 x 64 VALU tiles this replaces.
+// 64 weight rows per item (with the K of a stage split over two sets of
+// wavefronts, or three workgroups per CU) measured 5 to 15% slower.
+constexpr int FBM = 64, FBN = 128, FBK = 32, FST = 3;
+constexpr int kF32Waves = 8, kF32PerCu = 2;       // wavefronts; workgroups per CU
+constexpr int kF32Stage = (FBM + FBN) * FBK;      // floats of one stage
+constexpr int kF32Loads = (FBM + FBN) / 8 / kF32Waves;  // 8-row loads of one wavefront and stage
+static_assert(FBM / 8 == kF32Waves && FBN / 16 == kF32Waves, "one A load and one 16-row column per wavefront");
+static_assert(kF32Stage * 4 * FST * kF32PerCu + 1024 <= 160 * 1024, "LDS budget");
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-template <int MODE>
-__global__ __launch_bounds__(256) void grouped_gemm_f32(GroupedProblem p, WeightTable wt,
-                                                        const float* __restrict__ A,
-                                                        float* __restrict__ C) {
-  __shared__ float As[FBK][FBM + 4];
-  __shared__ float Bs[FBK][FBN + 4];
-  const int tile = blockIdx.x;
-  if (tile >= *p.n_tiles) return;
-  const int4 td = p.tiles[tile];  // the tile's group
-  const int key = td.x, row0 = td.y + (tile - td.w) * FBM;
-  const int ES = p.E + p.S;
-  const int layer = key / ES, e = key - layer * ES;
-  const int row_end = p.offsets[key + 1];
-  const int nt = blockIdx.y;
-  const int K = MODE == MODE_GATEUP ? p.H : p.F;
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const float* Bbase = MODE == MODE_GATEUP
-                           ? static_cast<const float*>(wt.gu[layer]) + (size_t)e * 2 * p.F * p.H
-                           : static_cast<const float*>(wt.dn[layer]) + (size_t)e * p.H * p.F;
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  const int arow = min(row0 + lr, p.P - 1);
-  int brow;
-  if (MODE == MODE_GATEUP) {
-    const int f = nt * 32 + (lr & 31);
-    brow = lr < 32 ? f : p.F + f;
-  } else {
-    brow = nt * FBN + lr;
-  }
-  const float* ap = A + (size_t)arow * K + lk;
-  const float* bp = Bbase + (size_t)brow * K + lk;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += FBK) {
-    const float4 av = *reinterpret_cast<const float4*>(ap + k0);
-    const float4 bv = *reinterpret_cast<const float4*>(bp + k0);
-    As[lk + 0][lr] = av.x; As[lk + 1][lr] = av.y; As[lk + 2][lr] = av.z; As[lk + 3][lr] = av.w;
-    Bs[lk + 0][lr] = bv.x; Bs[lk + 1][lr] = bv.y; Bs[lk + 2][lr] = bv.z; Bs[lk + 3][lr] = bv.w;
-    __syncthreads();
+struct F32Loop {
+  float* smem;
+  __amdgpu_buffer_rsrc_t ra, rb[2];  // A rows of the item; the wavefront's first / second 8 weight rows
+  int a_off, b_off[2];               // per-lane byte offset of a load's row and chunk
+  int wave, lrow, quarter, nk;
+};
+
+// Loads of stage s (K columns 32 s .. 32 s + 31) into ring slot `slot`:
+// wavefront w fills A rows 8 w .. + 7 and its own weight rows.  A row holds
+// eight 16-byte chunks, logical chunk c at c ^ ((row >> 1) & 7).
+__device__ __forceinline__ void f32_issue(const F32Loop& L, int s, int slot) {
+  float* st = L.smem + slot * kF32Stage;
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(L.ra, st + 8 * L.wave * FBK, 16, L.a_off, s * FBK * 4, 0, 0);
 #pragma unroll
-    for (int kk = 0; kk < FBK; ++kk) {
-      float a[4], b[4];
+  for (int j = 0; j < 2; ++j)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(L.rb[j], st + (FBM + 16 * L.wave + 8 * j) * FBK, 16, L.b_off[j],
+                                             s * FBK * 4, 0, 0);
+}
+
+// K loop over NACT active 16-row blocks.  Lane l reads 16-byte chunk
+// 4 kc + l / 16 of row l % 16 of each block, and element i of the chunks goes
+// to MFMA i: every MFMA sums K columns 16 kc + i + {0, 4, 8, 12}, the same
+// order for every row of every item.  The weights are the first operand, so
+// a lane holds four consecutive output columns of one token row.
+template <int NACT>
+__device__ __forceinline__ void f32_k_loop(const F32Loop& L, floatx4 (&acc)[FBM / 16]) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+  for (int s = 0; s < FST - 1; ++s) f32_issue(L, s, s);  // nk >= 4 (K is a multiple of 128)
+  const int sw = swz(L.lrow, 0), last = L.nk - 1;
+  int slot = 0;
+  for (int s = 0; s < L.nk; ++s) {
+    // this wavefront's loads of stage s have landed and its reads of stage
+    // s-1 are done before the barrier publishes the one and frees the other;
+    // past the last stage that one is loaded again into a slot nobody reads,
+    // so the count in flight is a constant
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    wait_vm<(FST - 2) * kF32Loads>();
+    bar();
+    f32_issue(L, min(s + FST - 1, last), slot == 0 ? FST - 1 : slot - 1);
+    const float* st = L.smem + slot * kF32Stage + L.lrow * FBK;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
+    for (int kc = 0; kc < FBK / 16; ++kc) {
+      const int ch = ((4 * kc + L.quarter) ^ sw) * 4;
+      floatx4 a[NACT];
+      const floatx4 b = *reinterpret_cast<const floatx4*>(st + (FBM + 16 * L.wave) * FBK + ch);
+#pragma unroll
+      for (int mb = 0; mb < NACT; ++mb) a[mb] = *reinterpret_cast<const floatx4*>(st + 16 * mb * FBK + ch);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+        for (int mb = 0; mb < NACT; ++mb)
+          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[i], a[mb][i], acc[mb], 0, 0, 0);
     }
-    __syncthreads();
+    slot = slot == FST - 1 ? 0 : slot + 1;
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = row0 + ty * 4 + i;
-    if (row >= row_end) continue;
+  wait_vm<0>();  // the reloads past the last stage, before the ring is written again
+}
+
+template <int MODE>
+__global__ __launch_bounds__(64 * kF32Waves, kF32Waves * kF32PerCu / 4) void grouped_gemm_f32(
+    GroupedProblem p, WeightTable wt, const float* __restrict__ A, float* __restrict__ C, int n_ntiles) {
+  // One array for the ring and the next item's index: with two LDS variables
+  // the compiler tells their accesses apart and then guards every fragment
+  // read with a wait for all loads into the ring.
+  __shared__ __attribute__((aligned(1024))) float smem[FST * kF32Stage + 4];
+  int* s_next = reinterpret_cast<int*>(smem + FST * kF32Stage);
+  // the ring is written by global->LDS loads the compiler does not see
+  asm volatile("" ::"v"(smem) : "memory");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lrow = lane & 15, quarter = lane >> 4;
+  const int K = MODE == MODE_GATEUP ? p.H : p.F;
+  const int ES = p.E + p.S;
+  ItemQueue q(p, (long long)(*p.n_tiles) * n_ntiles);
+  if (tid == 0) *s_next = q.settle(q.draw());
+  __syncthreads();
+  int it = __builtin_amdgcn_readfirstlane(*s_next);
+
+  while (it >= 0) {
+    int got = 0;
+    if (tid == 0) got = q.draw();
+    const int4 gd = uniform(p.tiles[it / n_ntiles]);  // key, first row, rows, first m-tile
+    const int mt = (gd.z + FBM - 1) / FBM;
+    const Tile2 tile = item_tile(it - gd.w * n_ntiles, mt, n_ntiles);
+    // the group's m-tiles share its rows evenly in whole 16-row blocks
+    const int rpt = 16 * ((gd.z + 16 * mt - 1) / (16 * mt));
+    const int row0 = gd.y + tile.mi * rpt, rows = min(gd.y + gd.z - row0, rpt);
+    const int layer = gd.x / ES, e = gd.x - layer * ES;
+    // the wavefront's 16 weight rows: two runs of 8
+    const float* B0;
+    const float* B1;
     if (MODE == MODE_GATEUP) {
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-        C[(size_t)row * p.F + nt * 32 + tx + 16 * jj] = swiglu(acc[i][jj], acc[i][jj + 2]);
+      B0 = static_cast<const float*>(wt.gu[layer]) + ((size_t)e * 2 * p.F + tile.ni * (FBN / 2) + 8 * wave) * K;
+      B1 = B0 + (size_t)p.F * K;
     } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) C[(size_t)row * p.H + nt * FBN + tx + 16 * j] = acc[i][j];
+      B0 = static_cast<const float*>(wt.dn[layer]) + ((size_t)e * p.H + tile.ni * FBN + 16 * wave) * K;
+      B1 = B0 + (size_t)8 * K;
     }
+    F32Loop L;
+    L.smem = smem;
+    L.ra = buffer_rsrc(A + (size_t)row0 * K, (uint32_t)(rows * K * 4));  // rows past the item's read zeros
+    L.rb[0] = buffer_rsrc(B0, (uint32_t)(8 * K * 4));
+    L.rb[1] = buffer_rsrc(B1, (uint32_t)(8 * K * 4));
+    {
+      const int lr = lane >> 3, c = (lane & 7) ^ (lr >> 1);  // chunk in an even 8-row block; odd ones flip bit 2
+      L.a_off = (8 * wave + lr) * K * 4 + (c ^ ((wave & 1) * 4)) * 16;
+      L.b_off[0] = lr * K * 4 + c * 16;
+      L.b_off[1] = lr * K * 4 + (c ^ 4) * 16;
+    }
+    L.wave = wave;
+    L.lrow = lrow;
+    L.quarter = quarter;
+    L.nk = K / FBK;
+    floatx4 acc[FBM / 16];
+#pragma unroll
+    for (int mb = 0; mb < FBM / 16; ++mb) acc[mb] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    const int nact = (rows + 15) >> 4;
+    switch (nact) {
+      case 1: f32_k_loop<1>(L, acc); break;
+      case 2: f32_k_loop<2>(L, acc); break;
+      case 3: f32_k_loop<3>(L, acc); break;
+      default: f32_k_loop<4>(L, acc); break;
+    }
+    // acc[mb][v]: token row 16 mb + lane % 16, weight row 4 (lane / 16) + v.
+    // Gate/up: the upper 32 lanes hold the up rows of the lower lanes' gate
+    // rows; the lower lanes finish even row blocks, the upper ones odd blocks.
+    const bool hi = quarter >= 2;
+#pragma unroll
+    for (int mb = 0; mb < FBM / 16; ++mb) {
+      if (mb >= nact) continue;
+      if constexpr (MODE == MODE_GATEUP) {
+        if (mb & 1) continue;
+        floatx4 g, u;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float x = __shfl_xor(hi ? acc[mb][v] : acc[mb + 1][v], 32, 64);
+          g[v] = hi ? x : acc[mb][v];
+          u[v] = hi ? acc[mb + 1][v] : x;
+        }
+        const int r = 16 * (mb + hi) + lrow;
+        if (r < rows)
+          *reinterpret_cast<float4*>(C + (size_t)(row0 + r) * p.F + tile.ni * (FBN / 2) + 8 * wave +
+                                     4 * (quarter & 1)) =
+              make_float4(swiglu(g[0], u[0]), swiglu(g[1], u[1]), swiglu(g[2], u[2]), swiglu(g[3], u[3]));
+      } else {
+        const int r = 16 * mb + lrow;
+        if (r < rows)
+          *reinterpret_cast<float4*>(C + (size_t)(row0 + r) * p.H + tile.ni * FBN + 16 * wave + 4 * quarter) =
+              make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
+      }
+    }
+    if (tid == 0) *s_next = q.settle(got);
+    __syncthreads();  // every wavefront is done with the ring; the next item is published
+    it = __builtin_amdgcn_readfirstlane(*s_next);
+    __syncthreads();  // and read, before the next one overwrites it
   }
 }
 
@@ -772,8 +910,8 @@ hipError_t launch_gateup(int dtype, const GroupedProblem& p, const WeightTable& 
                        p, wt, static_cast<const bf16_t*>(a_perm), static_cast<bf16_t*>(h),
                        p.F / (BN / 2));
   } else {
-    hipLaunchKernelGGL(grouped_gemm_f32<MODE_GATEUP>, dim3(p.max_tiles, p.F / 32), dim3(256), 0,
-                       s, p, wt, static_cast<const float*>(a_perm), static_cast<float*>(h));
+    hipLaunchKernelGGL(grouped_gemm_f32<MODE_GATEUP>, dim3(kF32PerCu * persistent_grid()), dim3(64 * kF32Waves), 0,
+                       s, p, wt, static_cast<const float*>(a_perm), static_cast<float*>(h), p.F / (FBN / 2));
   }
   prof_stop(EB_K_GATEUP, s);
   return hipGetLastError();
@@ -791,8 +929,8 @@ hipError_t launch_down(int dtype, const GroupedProblem& p, const WeightTable& wt
                          p.partial, n, p.P_live, p.H, static_cast<bf16_t*>(o));
     }
   } else {
-    hipLaunchKernelGGL(grouped_gemm_f32<MODE_DOWN>, dim3(p.max_tiles, p.H / FBN), dim3(256), 0, s,
-                       p, wt, static_cast<const float*>(h), static_cast<float*>(o));
+    hipLaunchKernelGGL(grouped_gemm_f32<MODE_DOWN>, dim3(kF32PerCu * persistent_grid()), dim3(64 * kF32Waves), 0, s,
+                       p, wt, static_cast<const float*>(h), static_cast<float*>(o), p.H / FBN);
   }
   prof_stop(EB_K_DOWN, s);
   return hipGetLastError();

@@ -1,0 +1,77 @@
+"""The grouped expert GEMMs at the edges of their tiles: groups of exactly the
+row counts where a tile, a row block or a kernel choice begins, against a plain
+float64 computation of the same experts (through the C ABI).
+
+Tolerance: the suite's own bar, max-abs error <= 1e-5 max|ref| (fp32) and
+1e-2 max|ref| (bf16, whose h and o are each rounded once to 8 bits)."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import assert_close, log
+
+pytestmark = pytest.mark.gpu
+
+
+def _step(device, dtype, H, F, E, S, lens, experts, seed=3):
+    """One layer of E routed (top-1) and S shared experts; micro-batch i's tokens all pick
+    experts[i].  Returns (o, h, a_perm) of the step and their float64 values."""
+    from paper_2608_07964_amd import binding as B
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=device).manual_seed(seed)
+    gu = (torch.randn(E + S, 2 * F, H, generator=g, device=device) * 0.05).to(tdt)
+    dn = (torch.randn(E + S, H, F, generator=g, device=device) * 0.05).to(tdt)
+    desc = B.make_desc(1, H, F, E, 1, S, 1, dtype)
+    pgu, pdn = torch.empty_like(gu), torch.empty_like(dn)
+    B.easybalance_pack_weights(desc, B.EB_WEIGHTS_GATE_UP, E + S, gu, pgu)
+    B.easybalance_pack_weights(desc, B.EB_WEIGHTS_DOWN, E + S, dn, pdn)
+    ents = []
+    for i, (T, e) in enumerate(zip(lens, experts)):
+        a = torch.randn(T, H, generator=g, device=device).to(tdt)
+        ents.append((i, 0, T, a, torch.full((T, 1), e, dtype=torch.int32, device=device),
+                     torch.ones(T, 1, device=device)))
+    P = sum(lens) * (1 + S)
+    nan = float("nan")
+    o = torch.full((P, H), nan, dtype=tdt, device=device)
+    views = dict(h=torch.full((P, F), nan, dtype=tdt, device=device),
+                 a_perm=torch.full((P, H), nan, dtype=tdt, device=device))
+    inv = torch.empty(P, dtype=torch.int32, device=device)
+    wsb = B.easybalance_moe_step_workspace_size(desc, list(lens))
+    ws = torch.empty(wsb + 256, dtype=torch.uint8, device=device)
+    B.easybalance_moe_step(desc, B.work_array(ents), len(ents), [pgu], [pdn],
+                           ws.data_ptr() + (-ws.data_ptr()) % 256, wsb, o, inv, views)
+    torch.cuda.synchronize()
+    # grouped order: experts ascending, then entries in order; shared slots last
+    rows = [torch.cat([en[3] for en, e in zip(ents, experts) if e == x]) if x in experts else None
+            for x in range(E)] + [torch.cat([en[3] for en in ents])] * S
+    ref_h, ref_o = [], []
+    for x, a in enumerate(rows):
+        if a is None:
+            continue
+        z = a.double() @ gu[x].double().t()
+        h = torch.nn.functional.silu(z[:, :F]) * z[:, F:]
+        ref_h.append(h)
+        ref_o.append(h.to(tdt).double() @ dn[x].double().t())
+    return (o, views["h"], views["a_perm"]), (torch.cat(ref_o), torch.cat(ref_h),
+                                              torch.cat([a for a in rows if a is not None]))
+
+
+def _check(got, ref, dtype, what):
+    for g, r, n in zip(got, ref, ("o", "h", "a_perm")):
+        assert_close(g.float().cpu().numpy(), r.float().cpu().numpy(), dtype, f"{what} {n}")
+
+
+# fp32 row blocks of 16, m-tiles of 64 sharing a group's rows evenly
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 33, 48, 63, 64, 65, 127, 129, 200, 513])
+def test_f32_group_rows(rows, device):
+    log(f"f32 rows {rows}")
+    got, ref = _step(device, "f32", 256, 384, 3, 1, [rows, 5], [1, 2])
+    _check(got, ref, "f32", f"rows {rows}")
+
+
+# fewest K stages (H = 256, F = 128) and column tiles; long K
+@pytest.mark.parametrize("H,F", [(256, 128), (512, 128), (256, 2176), (1280, 640)])
+def test_f32_shapes(H, F, device):
+    log(f"f32 H {H} F {F}")
+    got, ref = _step(device, "f32", H, F, 2, 0, [70, 9], [0, 1])
+    _check(got, ref, "f32", f"H {H} F {F}")
