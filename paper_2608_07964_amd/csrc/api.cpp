@@ -51,10 +51,11 @@ struct StepShape {
   long long P;         // grouped rows
   long long tokens;
   int max_tiles;
+  long long layer_tokens;  // the most tokens at one layer (at least; the buffers' bound)
 };
 
 StepShape step_shape(const eb_model_desc& d, int n_run, const int32_t* T) {
-  StepShape s{0, 0, 0, 0};
+  StepShape s{0, 0, 0, 0, 0};
   for (int i = 0; i < n_run; ++i) {
     s.n_chunks += (T[i] + kPermChunk - 1) / kPermChunk;
     s.tokens += T[i];
@@ -63,12 +64,12 @@ StepShape step_shape(const eb_model_desc& d, int n_run, const int32_t* T) {
   const long long bm = gemm_bm(d.dtype);
   const long long groups = (long long)n_run * (d.E + d.S);
   s.max_tiles = (int)((s.P + bm - 1) / bm + (groups < s.P ? groups : s.P));
+  s.layer_tokens = s.tokens;  // callers that know the entries' layers narrow it
   return s;
 }
 
 struct WsLayout {
-  size_t hist, chunk_base, offsets, tiles, n_tiles, groups, n_groups, work_ctr, partial, perm, a_perm,
-      h, total;
+  size_t hist, chunk_base, offsets, tiles, work_ctr, partial, perm, a_perm, h, total;
 };
 
 WsLayout ws_layout(const eb_model_desc& d, const StepShape& s, const eb_step_views* v) {
@@ -84,10 +85,7 @@ WsLayout ws_layout(const eb_model_desc& d, const StepShape& s, const eb_step_vie
   w.chunk_base = take(sizeof(int32_t) * (size_t)s.n_chunks * (d.E + d.S));
   w.offsets = (v && v->offsets) ? 0 : take(sizeof(int32_t) * ((size_t)d.L * (d.E + d.S) + 1));
   w.tiles = take(sizeof(int4) * (size_t)(s.max_tiles > 0 ? s.max_tiles : 1));
-  w.n_tiles = take(sizeof(int32_t));
-  w.groups = take(sizeof(int4) * (size_t)d.L * (d.E + d.S));
-  w.n_groups = take(sizeof(int32_t));
-  w.work_ctr = take(sizeof(int32_t) * kWorkCounters);
+  w.work_ctr = take(sizeof(int32_t) * kWorkWords);
   w.partial = down_ksplit(d.dtype, d.F) > 1 ? take(sizeof(float) * 2 * (size_t)s.P * d.H) : 0;
   w.perm = (v && v->perm) ? 0 : take(sizeof(int32_t) * (size_t)s.P);
   w.a_perm = (v && v->a_perm) ? 0 : take(eb * (size_t)s.P * d.H);
@@ -163,9 +161,6 @@ StepWs carve_step(const eb_model_desc& d, const StepShape& sh, const eb_step_vie
   b.chunk_base = reinterpret_cast<int32_t*>(base + L.chunk_base);
   b.offsets = (views && views->offsets) ? views->offsets : reinterpret_cast<int32_t*>(base + L.offsets);
   b.tiles = reinterpret_cast<int4*>(base + L.tiles);
-  b.n_tiles = reinterpret_cast<int32_t*>(base + L.n_tiles);
-  b.groups = reinterpret_cast<int4*>(base + L.groups);
-  b.n_groups = reinterpret_cast<int32_t*>(base + L.n_groups);
   b.work_ctr = reinterpret_cast<int32_t*>(base + L.work_ctr);
   b.max_tiles = sh.max_tiles;
   b.perm = (views && views->perm) ? views->perm : reinterpret_cast<int32_t*>(base + L.perm);
@@ -189,16 +184,14 @@ int run_gemms(const eb_model_desc& d, const StepShape& sh, const StepWs& w, cons
   gp.offsets = w.b.offsets;
   gp.P_live = w.b.offsets + (size_t)d.L * (d.E + d.S);
   gp.tiles = w.b.tiles;
-  gp.n_tiles = w.b.n_tiles;
-  gp.groups = w.b.groups;
-  gp.n_groups = w.b.n_groups;
-  gp.max_tiles = sh.max_tiles;
+  gp.n_tiles = w.b.work_ctr + kWorkTiles;
+  gp.layer_tokens = (int32_t)sh.layer_tokens;
   gp.work_ctr = w.b.work_ctr;
   gp.ksplit = 1;
   gp.partial = nullptr;
   int rc;
   if ((rc = hip_status(launch_gateup(d.dtype, gp, wt, w.b.a_perm, w.h, s), "gate/up GEMM"))) return rc;
-  gp.work_ctr = w.b.work_ctr + kWorkCounters / 2;
+  gp.work_ctr = w.b.work_ctr + kWorkDown;
   gp.ksplit = down_ksplit(d.dtype, d.F);
   gp.partial = w.partial;
   return hip_status(launch_down(d.dtype, gp, wt, w.h, o, s, sum_halves), "down GEMM");
@@ -358,8 +351,14 @@ int moe_step_common(const eb_model_desc* desc, int32_t n_run, const eb_work* run
   const eb_model_desc& d = *desc;
   int32_t Ts[EB_MAX_RUN];  // no heap allocation on this path (n_run <= EB_MAX_RUN, checked)
   for (int i = 0; i < n_run; ++i) Ts[i] = run[i].T;
-  const StepShape sh = step_shape(d, n_run, Ts);
+  StepShape sh = step_shape(d, n_run, Ts);
   if (sh.P == 0) return EB_OK;
+  sh.layer_tokens = 0;
+  for (int i = 0; i < n_run; ++i) {
+    long long t = 0;
+    for (int j = 0; j < n_run; ++j) t += run[j].layer == run[i].layer ? run[j].T : 0;
+    if (t > sh.layer_tokens) sh.layer_tokens = t;
+  }
   if (W_gu == nullptr || W_dn == nullptr) return set_error(EB_ERR_INVALID_ARG, "W_gu/W_dn is NULL");
   WeightTable wt;
   memset(&wt, 0, sizeof(wt));
@@ -389,8 +388,7 @@ int moe_step_common(const eb_model_desc* desc, int32_t n_run, const eb_work* run
   const int eb = d.dtype == EB_DTYPE_BF16 ? 2 : 4;
   const StepBuffers& b = w.b;
   if ((rc = hip_status(launch_perm_count(rt, sh.n_chunks, b.hist, s), "perm_count"))) return rc;
-  if ((rc = hip_status(launch_perm_scan(rt, b.hist, b.chunk_base, b.offsets, b.tiles, b.n_tiles, b.groups,
-                                        b.n_groups, gemm_bm(d.dtype), b.max_tiles, b.work_ctr, s),
+  if ((rc = hip_status(launch_perm_scan(rt, b.hist, b.chunk_base, b.offsets, b.tiles, gemm_bm(d.dtype), b.max_tiles, b.work_ctr, s),
                        "perm_scan")))
     return rc;
   if ((rc = hip_status(launch_perm_scatter(rt, sh.n_chunks, eb, b.chunk_base, b.perm, inv_out, b.a_perm, s),

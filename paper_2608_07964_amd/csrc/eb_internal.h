@@ -57,10 +57,9 @@ struct GroupedProblem {
   const int4* tiles;                       // [n_tiles] the row block's group: (key, first row,
                                            // rows, index of the group's first row block)
   const int32_t* n_tiles;                  // device scalar: row blocks over all groups
-  const int4* groups;                      // [n_groups] (key, first row, rows, first row block)
-  const int32_t* n_groups;                 // device scalar: non-empty keys
-  int32_t max_tiles;                       // grid bound
-  int32_t* work_ctr;                       // [8] per-XCD work counters of this launch, zeroed
+  int32_t layer_tokens;                    // the most tokens the step has at one layer
+  int32_t* work_ctr;                       // per-XCD work counters of this launch, zeroed:
+                                           // XCD x's at work_ctr[x * kWorkStride]
   int32_t ksplit;                          // 1, or 2: K halves computed by separate items
   float* partial;                          // ksplit 2: [2][P][N] fp32 partial sums
 };
@@ -69,7 +68,11 @@ struct GroupedProblem {
 // so every schedule computes a row the same way).
 inline int down_ksplit(int dtype, int F) { return dtype == EB_DTYPE_BF16 && F >= 8192 ? 2 : 1; }
 
-constexpr int kWorkCounters = 16;          // 8 per grouped GEMM launch (gate/up, down)
+// Step counters: one 128-byte line per XCD holding its work counter of the
+// gate/up launch and (kWorkDown on) of the down launch; the number of row
+// blocks follows in the first line.
+constexpr int kWorkStride = 32, kWorkDown = 8, kWorkTiles = 16;
+constexpr int kWorkWords = 8 * kWorkStride;
 
 // Device-side entry lookup: largest rho with base[rho] <= v (bases ascending).
 __device__ __forceinline__ int find_entry(const int32_t* base, int n, int v) {
@@ -181,8 +184,7 @@ hipError_t launch_route(const eb_model_desc& d, int T, const float* x, const flo
 
 hipError_t launch_perm_count(const RunTable& rt, int n_chunks, int32_t* hist, hipStream_t s);
 hipError_t launch_perm_scan(const RunTable& rt, const int32_t* hist, int32_t* chunk_base,
-                            int32_t* offsets, int4* tiles, int32_t* n_tiles, int4* groups,
-                            int32_t* n_groups, int bm, int max_tiles, int32_t* work_ctr,
+                            int32_t* offsets, int4* tiles, int bm, int max_tiles, int32_t* work_ctr,
                             hipStream_t s);
 hipError_t launch_perm_scatter(const RunTable& rt, int n_chunks, int elem_bytes,
                                const int32_t* chunk_base, int32_t* perm, int32_t* inv,
@@ -194,10 +196,7 @@ struct StepBuffers {
   int32_t* chunk_base;
   int32_t* offsets;
   int4* tiles;
-  int32_t* n_tiles;
-  int4* groups;
-  int32_t* n_groups;
-  int32_t* work_ctr;
+  int32_t* work_ctr;       // [kWorkWords]
   int32_t max_tiles;
   int32_t* perm;
   int32_t* inv;

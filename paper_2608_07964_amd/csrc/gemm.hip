@@ -556,6 +556,10 @@ __device__ __forceinline__ Tile2 item_tile(int local, int mt, int n_ntiles) {
 }
 
 // One thread's view of the item counters: the XCD whose range it draws from.
+// Each XCD's counter has a cache line of its own, and another XCD's counter is
+// read before it is drawn from: when every workgroup drew from all eight in
+// one line on its way out, those 2000 atomics ran one after the other for
+// about 20 us at the end of each launch.
 struct ItemQueue {
   int32_t* ctr;
   long long total;
@@ -563,14 +567,16 @@ struct ItemQueue {
   __device__ __forceinline__ ItemQueue(const GroupedProblem& p, long long total_)
       : ctr(p.work_ctr), total(total_), xcd(blockIdx.x % kXcds), victim(blockIdx.x % kXcds) {}
   __device__ __forceinline__ int range_lo(int x) const { return (int)((x * total) / kXcds); }
-  __device__ __forceinline__ int draw() const { return atomicAdd(&ctr[victim], 1); }
+  __device__ __forceinline__ int draw() const { return atomicAdd(&ctr[victim * kWorkStride], 1); }
   // item index from a value drawn from victim's counter, or -1 once every range is drained
   __device__ __forceinline__ int settle(int got) {
     int it = range_lo(victim) + got;
     while (it >= range_lo(victim + 1)) {
       victim = victim + 1 == kXcds ? 0 : victim + 1;
       if (victim == xcd) return -1;
-      it = range_lo(victim) + draw();
+      it = range_lo(victim) +
+           __hip_atomic_load(&ctr[victim * kWorkStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (it < range_lo(victim + 1)) it = range_lo(victim) + draw();
     }
     return it;
   }

@@ -6,10 +6,10 @@
 //
 //   perm_count_kernel    per 256-token chunk: routed pairs per expert (LDS atomics)
 //   perm_scan_kernel     one workgroup: per-key totals, offsets, per-chunk bases,
-//                        the GEMM tile list (each BM-row block's group record) and
-//                        the list of non-empty groups (key, first row, rows,
-//                        index of its first row block); it also clears the
-//                        work counters of the step's grouped GEMM launches
+//                        the GEMM tile list (each BM-row block's group record:
+//                        key, first row, rows, index of its first row block);
+//                        it also clears the work counters of the step's
+//                        grouped GEMM launches
 //   perm_scatter_kernel  per chunk: stable rank of each pair inside its key from
 //                        per-wavefront 64-bit expert masks (popcount of the lanes
 //                        below), then inv and perm
@@ -88,8 +88,7 @@ __device__ int block_exclusive_scan(int v, int* wtot, int* total) {
 template <class RTA>
 __global__ __launch_bounds__(kScanThreads) void perm_scan_kernel(
     RTA rta, const int32_t* __restrict__ hist, int32_t* __restrict__ chunk_base,
-    int32_t* __restrict__ offsets, int4* __restrict__ tiles, int32_t* __restrict__ n_tiles,
-    int4* __restrict__ groups, int32_t* __restrict__ n_groups, int bm, int max_tiles,
+    int32_t* __restrict__ offsets, int4* __restrict__ tiles, int bm, int max_tiles,
     int32_t* __restrict__ work_ctr) {
   __shared__ int running[kMaxKeys];              // per-key totals, then offsets / cursors
   __shared__ int hl[kHistWindow];                // one window of histogram cells
@@ -97,7 +96,7 @@ __global__ __launch_bounds__(kScanThreads) void perm_scan_kernel(
   __shared__ int s_cb[EB_MAX_RUN + 1], s_tb[EB_MAX_RUN + 1], s_ly[EB_MAX_RUN];
   const RunTable& rt = rta.get();
   const int tid = threadIdx.x;
-  if (tid < kWorkCounters) work_ctr[tid] = 0;
+  if (tid < kWorkWords && tid != kWorkTiles) work_ctr[tid] = 0;
   const int E = rt.E, ES = rt.E + rt.S, n = rt.n;
   const int n_chunks = rt.chunk_base[n];
   const int n_keys = rt.L * ES;
@@ -149,31 +148,22 @@ __global__ __launch_bounds__(kScanThreads) void perm_scan_kernel(
   if (tid == 0) offsets[n_keys] = total;
   __syncthreads();
 
-  // 3) tile and group lists: ceil(M/bm) row blocks per non-empty key, keys ascending
+  // 3) tile list: ceil(M/bm) row blocks per non-empty key, keys ascending
   auto rows_of = [&](int i) { return (i + 1 < n_keys ? running[i + 1] : total) - running[i]; };
-  int local_tiles = 0, local_groups = 0;
-  for (int i = k0; i < k1; ++i) {
-    const int M = rows_of(i);
-    local_tiles += (M + bm - 1) / bm;
-    local_groups += M > 0;
-  }
-  int tiles_total = 0, groups_total = 0;
+  int local_tiles = 0;
+  for (int i = k0; i < k1; ++i) local_tiles += (rows_of(i) + bm - 1) / bm;
+  int tiles_total = 0;
   int tb = block_exclusive_scan(local_tiles, wtot, &tiles_total);
-  int gb = block_exclusive_scan(local_groups, wtot, &groups_total);
   for (int i = k0; i < k1; ++i) {
     const int r0 = running[i], M = rows_of(i);
     if (M == 0) continue;
     const int4 g = make_int4(i, r0, M, tb);
-    groups[gb++] = g;
     for (int m = 0; m < M; m += bm) {
       if (tb < max_tiles) tiles[tb] = g;
       ++tb;
     }
   }
-  if (tid == 0) {
-    *n_tiles = min(tiles_total, max_tiles);
-    *n_groups = groups_total;
-  }
+  if (tid == 0) work_ctr[kWorkTiles] = min(tiles_total, max_tiles);
   __syncthreads();  // running[] becomes the cursors below
 
   // 4) per-chunk bases: for every column, the entries' chunks in order; a
@@ -306,11 +296,10 @@ void perm_count_impl(RTA a, int grid, int32_t* hist, hipStream_t s) {
 
 template <class RTA>
 void perm_scan_impl(RTA a, const int32_t* hist, int32_t* chunk_base, int32_t* offsets, int4* tiles,
-                    int32_t* n_tiles, int4* groups, int32_t* n_groups, int bm, int max_tiles,
-                    int32_t* work_ctr, hipStream_t s) {
+                    int bm, int max_tiles, int32_t* work_ctr, hipStream_t s) {
   prof_start(EB_K_PERM_SCAN, s);
   hipLaunchKernelGGL(perm_scan_kernel<RTA>, dim3(1), dim3(kScanThreads), 0, s, a, hist, chunk_base,
-                     offsets, tiles, n_tiles, groups, n_groups, bm, max_tiles, work_ctr);
+                     offsets, tiles, bm, max_tiles, work_ctr);
   prof_stop(EB_K_PERM_SCAN, s);
 }
 
@@ -348,12 +337,10 @@ hipError_t launch_perm_count(const RunTable& rt, int n_chunks, int32_t* hist, hi
 }
 
 hipError_t launch_perm_scan(const RunTable& rt, const int32_t* hist, int32_t* chunk_base,
-                            int32_t* offsets, int4* tiles, int32_t* n_tiles, int4* groups,
-                            int32_t* n_groups, int bm, int max_tiles, int32_t* work_ctr,
+                            int32_t* offsets, int4* tiles, int bm, int max_tiles, int32_t* work_ctr,
                             hipStream_t s) {
   if (!scan_fits(rt.L, rt.E, rt.S, rt.n)) return hipErrorInvalidValue;
-  perm_scan_impl(ByValue<RunTable>{rt}, hist, chunk_base, offsets, tiles, n_tiles, groups, n_groups,
-                 bm, max_tiles, work_ctr, s);
+  perm_scan_impl(ByValue<RunTable>{rt}, hist, chunk_base, offsets, tiles, bm, max_tiles, work_ctr, s);
   return hipGetLastError();
 }
 
@@ -371,8 +358,7 @@ hipError_t launch_permute_dev(const eb_model_desc& d, const RunTable* rt, int ma
   const InMemory<RunTable> a{rt};
   const int eb = d.dtype == EB_DTYPE_BF16 ? 2 : 4;
   perm_count_impl(a, max_chunks, b.hist, s);
-  perm_scan_impl(a, b.hist, b.chunk_base, b.offsets, b.tiles, b.n_tiles, b.groups, b.n_groups,
-                 gemm_bm(d.dtype), b.max_tiles, b.work_ctr, s);
+  perm_scan_impl(a, b.hist, b.chunk_base, b.offsets, b.tiles, gemm_bm(d.dtype), b.max_tiles, b.work_ctr, s);
   perm_scatter_impl(a, d.H, max_chunks, max_tokens, eb, b.chunk_base, b.perm, b.inv,
                     b.a_perm, s);
   return hipGetLastError();
