@@ -543,6 +543,21 @@ __device__ __forceinline__ int4 uniform(int4 v) {
                    __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
 }
 
+// The same for a buffer descriptor's base.
+__device__ __forceinline__ const bf16_t* uniform(const bf16_t* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (const bf16_t*)(((uint64_t)hi << 32) | lo);
+}
+
+// A group record by a scalar load (i uniform): it does not queue behind the
+// vector loads in flight.  The records are written by an earlier launch.
+__device__ __forceinline__ int4 scalar_record(const int4* p, int i) {
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  const i32x4 v = reinterpret_cast<const __attribute__((address_space(4))) i32x4*>((uintptr_t)p)[i];
+  return make_int4(v.x, v.y, v.z, v.w);
+}
+
 // Position of an item inside its group's list: column tile and m-tile.
 struct Tile2 {
   int ni, mi;
@@ -641,6 +656,208 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
     it = *s_next;
     __syncthreads();  // every thread has read it before the next prologue refills the ring
   }
+}
+
+// ---------------------------------------------------------------------------
+// Decode launches (bf16): every group has a few rows, so the launch does
+// nothing but stream the experts' weights once.  Each wavefront is a stream of
+// its own: a workgroup is one wavefront with a 40 KB LDS ring (four per CU)
+// and no barrier anywhere.  A unit is one 64-weight-row column of a 256-row
+// column tile (a contiguous 8 KB of every packed block) for up to 8 NA token
+// rows; each stage's ring slot holds the unit's A rows (NA KB) and B rows
+// (8 KB).  The stages of consecutive units form one sequence: while a unit's
+// last stages are multiplied, the first stages of the wavefront's next unit
+// are already being loaded, so a unit's end costs its stores and nothing else.
+// Each output is the same chain of MFMAs as in grouped_gemm_bf16, bit for bit.
+//
+// Bound by HBM: 74 groups of 2 to 31 rows at H = 2048, F = 1408 stream their
+// weights at 5.7 (gate/up, 149 us) and 5.5 TB/s (down, 76 us), against 162 and
+// 87 us in 256-column items on whole-CU workgroups; one token with 8 expert
+// slots 18 and 11 against 28 and 21 us (four times the units, so every CU
+// has some).  Five wavefronts of 32 KB per CU, three of 53 KB or two of 80 KB
+// measured 0 to 5% slower.
+constexpr int kStreamLds = 40 * 1024, kStreamPerCu = 4;
+template <int NA>
+struct StreamCfg {
+  static constexpr int SLOT = (NA + 8) * 512;       // elements of one stage (A rows, then B rows)
+  static constexpr int FIT = kStreamLds / (2 * SLOT), R = FIT > 4 ? 4 : FIT;  // ring slots
+  static constexpr int LOADS = NA + 8;              // 1 KB loads of one stage
+  static_assert(R >= 3 && (R - 2) * LOADS < 64, "ring");
+};
+constexpr int kStreamMinStages = 4;                 // K stages a unit needs for the look-ahead (R - 1, plus one)
+
+// What a stream loads next: the unit's descriptors and its next K stage.
+struct StreamUnit {
+  int tile_row0, rows;             // token rows of the unit's chunk
+  int row_end;                     // end of the m-tile's rows (chunks follow while rows remain)
+  int col;                         // 64-weight-row column of the expert matrix
+  int kh;                          // K part
+  const bf16_t* B;                 // expert matrix
+};
+
+template <int MODE, int NA>
+__global__ __launch_bounds__(64, 1) void stream_gemm_bf16(GroupedProblem p, WeightTable wt,
+                                                          const bf16_t* __restrict__ A, bf16_t* __restrict__ C) {
+  using Cfg = StreamCfg<NA>;
+  constexpr int R = Cfg::R, LOADS = Cfg::LOADS;
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[kStreamLds / 2];
+  // the ring is written by global->LDS loads the compiler does not see
+  asm volatile("" ::"v"(smem) : "memory");
+  const int lane = threadIdx.x, lrow = lane & 31, khalf = lane >> 5;
+  const int K = MODE == MODE_GATEUP ? p.H : p.F;
+  const int n_rows = MODE == MODE_GATEUP ? 2 * p.F : p.H;
+  const int ksplit = MODE == MODE_DOWN ? p.ksplit : 1;
+  const int n_cols = n_rows / 64, nsub = n_cols * ksplit, nk = K / BK / ksplit;
+  const int ES = p.E + p.S;
+  const int b_stage = (n_rows / BN) * (BN * BK * 2);  // bytes from one K stage's blocks to the next one's
+
+  // Units: XCD x owns a contiguous eighth of the list and its wavefronts take
+  // every per_xcd-th unit of it.  Units all cost the same, so a counter would
+  // balance nothing, and a thousand wavefronts drawing from counters in one
+  // cache line took 60 us.
+  const long long total = (long long)(*p.n_tiles) * nsub;
+  const int xcd = blockIdx.x % kXcds, per_xcd = gridDim.x / kXcds;
+  const int u_end = (int)(((xcd + 1) * total) / kXcds);
+
+  auto decode = [&](int unit) {
+    StreamUnit d;
+    const int u = __builtin_amdgcn_readfirstlane(unit);
+    const int4 gd = scalar_record(p.tiles, u / nsub);  // key, first row, rows, first m-tile
+    const int mt = (gd.z + BM - 1) / BM;
+    const int local = u - gd.w * nsub;           // K part, then column, m-tile fastest
+    d.kh = local / (mt * n_cols);
+    const int rem = local - d.kh * mt * n_cols;
+    d.col = rem / mt;
+    const int rpt = 32 * ((gd.z + 32 * mt - 1) / (32 * mt));
+    d.tile_row0 = gd.y + (rem - d.col * mt) * rpt;
+    d.row_end = min(gd.y + gd.z, d.tile_row0 + rpt);
+    d.rows = min(8 * NA, d.row_end - d.tile_row0);
+    const int layer = gd.x / ES, e = gd.x - layer * ES;
+    d.B = (MODE == MODE_GATEUP ? static_cast<const bf16_t*>(wt.gu[layer]) : static_cast<const bf16_t*>(wt.dn[layer])) +
+          (size_t)e * n_rows * K;
+    return d;
+  };
+
+  // load cursor
+  __amdgpu_buffer_rsrc_t ra, rb;
+  int a_soff = 0, b_voff = 0;  // next stage's A byte offset (uniform) and this lane's B byte offset
+  const int lr = lane >> 3, c_even = (lane & 7) ^ (lr >> 1);
+  const int a_even = lr * K * 2 + c_even * 16, a_odd = lr * K * 2 + (c_even ^ 4) * 16;
+  auto aim = [&](const StreamUnit& d, bool any) {  // any false: no next unit, loads of an empty buffer
+    // rows past the chunk read zeros
+    ra = buffer_rsrc(uniform(A + (size_t)d.tile_row0 * K + (size_t)d.kh * nk * BK),
+                     __builtin_amdgcn_readfirstlane(any ? d.rows * K * 2 - d.kh * nk * BK * 2 : 0));
+    rb = buffer_rsrc(uniform(d.B + (size_t)d.kh * nk * (b_stage / 2) + (size_t)(d.col >> 2) * (BN * BK) +
+                             (d.col & 3) * (64 * BK)),
+                     __builtin_amdgcn_readfirstlane(any ? (nk - 1) * b_stage + 64 * BK * 2 : 0));
+    a_soff = 0;
+    b_voff = lane * 16;
+  };
+  auto issue = [&](int slot) {
+    bf16_t* st = smem + slot * Cfg::SLOT;
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, st + j * 512, 16, 8 * j * K * 2 + ((j & 1) ? a_odd : a_even), a_soff,
+                                               0, 0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, st + (NA + j) * 512, 16, b_voff + j * 1024, 0, 0, 0);
+    a_soff += BK * 2;
+    b_voff += b_stage;
+  };
+
+  int u = (int)((xcd * total) / kXcds) + (int)(blockIdx.x / kXcds);
+  if (u >= u_end) return;
+  StreamUnit cur = decode(u);
+  aim(cur, true);
+#pragma unroll
+  for (int s = 0; s < R - 1; ++s) issue(s);
+  int slot = 0;
+  floatx16 acc[2];
+  const int sw = (lrow >> 1) & 7;
+  // one stage: its loads have landed, the slot of the stage before is free
+  // (its fragment reads are done), the load cursor's next stage goes there
+  auto step = [&]() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    wait_vm<(R - 2) * LOADS>();
+    asm volatile("" ::: "memory");
+    issue(slot == 0 ? R - 1 : slot - 1);
+    const bf16_t* sa = smem + slot * Cfg::SLOT + lrow * BK;  // rows past 8 NA: other rows, results discarded
+    const bf16_t* sb = smem + slot * Cfg::SLOT + NA * 512 + lrow * BK;
+    bf16x8 a[4], b[2][4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int ch = ((2 * ks + khalf) ^ sw) * 8;
+      a[ks] = *reinterpret_cast<const bf16x8*>(sa + ch);
+      b[0][ks] = *reinterpret_cast<const bf16x8*>(sb + ch);
+      b[1][ks] = *reinterpret_cast<const bf16x8*>(sb + 32 * BK + ch);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[nb][ks], a[ks], acc[nb], 0, 0, 0);
+    slot = slot == R - 1 ? 0 : slot + 1;
+  };
+
+  for (;;) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[nb][v] = 0.f;
+    for (int s = 0; s < nk - (R - 1); ++s) step();
+    // the load cursor moves on to the wavefront's next unit; a group with more
+    // rows than the launch was sized for (a caller's token that picks an
+    // expert twice) first goes on with its next rows
+    StreamUnit nxt = cur;
+    bool more = true;
+    if (cur.tile_row0 + 8 * NA < cur.row_end) {
+      nxt.tile_row0 += 8 * NA;
+      nxt.rows = min(8 * NA, cur.row_end - nxt.tile_row0);
+    } else {
+      u += per_xcd;
+      more = u < u_end;
+      if (more) nxt = decode(u);
+    }
+    aim(nxt, more);
+#pragma unroll
+    for (int s = 0; s < R - 1; ++s) step();
+    // acc[nb][4 g + q]: token row lrow, weight row 32 nb + 8 g + 4 khalf + q of the column
+    if (lrow < cur.rows) {
+      const size_t row = cur.tile_row0 + lrow;
+      if constexpr (MODE == MODE_GATEUP) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          uint2 v;
+          v.x = pack_bf16x2(swiglu(acc[0][4 * g], acc[1][4 * g]), swiglu(acc[0][4 * g + 1], acc[1][4 * g + 1]));
+          v.y = pack_bf16x2(swiglu(acc[0][4 * g + 2], acc[1][4 * g + 2]), swiglu(acc[0][4 * g + 3], acc[1][4 * g + 3]));
+          *reinterpret_cast<uint2*>(C + row * p.F + cur.col * 32 + 8 * g + 4 * khalf) = v;
+        }
+      } else {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const floatx16& c = acc[nb];
+            const int n = cur.col * 64 + nb * 32 + 8 * g + 4 * khalf;
+            if (ksplit > 1) {
+              *reinterpret_cast<float4*>(p.partial + ((size_t)cur.kh * p.P + row) * p.H + n) =
+                  make_float4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
+            } else {
+              uint2 v;
+              v.x = pack_bf16x2(c[4 * g], c[4 * g + 1]);
+              v.y = pack_bf16x2(c[4 * g + 2], c[4 * g + 3]);
+              *reinterpret_cast<uint2*>(C + row * p.H + n) = v;
+            }
+          }
+      }
+    }
+    if (!more) break;
+    cur = nxt;
+
+  }
+  wait_vm<0>();  // no load may write LDS after the wavefront has ended
 }
 
 // ---------------------------------------------------------------------------
@@ -908,10 +1125,31 @@ static int persistent_grid() {
   return grid;
 }
 
+// Whether a launch's groups are so small that it only streams weights: at
+// most 32 tokens at any layer (one MFMA block of rows), and K long enough for
+// the streams' look-ahead.  Up to 64 tokens (two blocks, 16 KB ring slots) the
+// 256-column items measured the same or faster.
+static bool stream_launch(const GroupedProblem& p) {
+  return p.layer_tokens <= 32 && p.H / BK >= kStreamMinStages && p.F / BK / p.ksplit >= kStreamMinStages;
+}
+
+template <int MODE, int NA>
+static void launch_stream_na(const GroupedProblem& p, const WeightTable& wt, const bf16_t* A, bf16_t* C, hipStream_t s) {
+  hipLaunchKernelGGL((stream_gemm_bf16<MODE, NA>), dim3(kStreamPerCu * persistent_grid()), dim3(64), 0, s, p, wt, A, C);
+}
+template <int MODE>
+static void launch_stream(const GroupedProblem& p, const WeightTable& wt, const bf16_t* A, bf16_t* C, hipStream_t s) {
+  if (p.layer_tokens <= 8) launch_stream_na<MODE, 1>(p, wt, A, C, s);
+  else if (p.layer_tokens <= 16) launch_stream_na<MODE, 2>(p, wt, A, C, s);
+  else launch_stream_na<MODE, 4>(p, wt, A, C, s);
+}
+
 hipError_t launch_gateup(int dtype, const GroupedProblem& p, const WeightTable& wt,
                          const void* a_perm, void* h, hipStream_t s) {
   prof_start(EB_K_GATEUP, s);
-  if (dtype == EB_DTYPE_BF16) {
+  if (dtype == EB_DTYPE_BF16 && stream_launch(p)) {
+    launch_stream<MODE_GATEUP>(p, wt, static_cast<const bf16_t*>(a_perm), static_cast<bf16_t*>(h), s);
+  } else if (dtype == EB_DTYPE_BF16) {
     hipLaunchKernelGGL(grouped_gemm_bf16<MODE_GATEUP>, dim3(persistent_grid()), dim3(kThreads), 0, s,
                        p, wt, static_cast<const bf16_t*>(a_perm), static_cast<bf16_t*>(h),
                        p.F / (BN / 2));
@@ -927,8 +1165,11 @@ hipError_t launch_down(int dtype, const GroupedProblem& p, const WeightTable& wt
                        void* o, hipStream_t s, bool sum_halves) {
   prof_start(EB_K_DOWN, s);
   if (dtype == EB_DTYPE_BF16) {
-    hipLaunchKernelGGL(grouped_gemm_bf16<MODE_DOWN>, dim3(persistent_grid()), dim3(kThreads), 0, s,
-                       p, wt, static_cast<const bf16_t*>(h), static_cast<bf16_t*>(o), p.H / BN);
+    if (stream_launch(p))
+      launch_stream<MODE_DOWN>(p, wt, static_cast<const bf16_t*>(h), static_cast<bf16_t*>(o), s);
+    else
+      hipLaunchKernelGGL(grouped_gemm_bf16<MODE_DOWN>, dim3(persistent_grid()), dim3(kThreads), 0, s,
+                         p, wt, static_cast<const bf16_t*>(h), static_cast<bf16_t*>(o), p.H / BN);
     if (p.ksplit > 1 && sum_halves) {
       const long long n = (long long)p.P * p.H;
       hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s,

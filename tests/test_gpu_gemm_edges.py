@@ -61,6 +61,63 @@ def _check(got, ref, dtype, what):
         assert_close(g.float().cpu().numpy(), r.float().cpu().numpy(), dtype, f"{what} {n}")
 
 
+# decode launches: at most 32 tokens at a layer (row loads of 8, 16 and 32), one
+# K part (F = 384) and two (F = 8192); 33 tokens take the tiled kernel
+@pytest.mark.parametrize("H,F", [(256, 384), (768, 8192)])
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 16, 17, 31, 32, 33])
+def test_bf16_decode_rows(rows, H, F, device):
+    log(f"bf16 rows {rows} H {H} F {F}")
+    lens, experts = ([rows], [1]) if rows < 3 else ([rows - 2, 2], [1, 2])
+    got, ref = _step(device, "bf16", H, F, 3, 1, lens, experts)
+    _check(got, ref, "bf16", f"rows {rows}")
+
+
+def test_bf16_decode_repeated_pick(device):
+    """Two micro-batches whose tokens pick one expert in all four slots: its group
+    spans 128 rows (16 of each 64 defined) while the layer has 32 tokens."""
+    from paper_2608_07964_amd import binding as B
+    T, k, H, F, E = 16, 4, 512, 384, 4
+    log("bf16 repeated pick")
+    g = torch.Generator(device=device).manual_seed(5)
+    gu = (torch.randn(E, 2 * F, H, generator=g, device=device) * 0.05).bfloat16()
+    dn = (torch.randn(E, H, F, generator=g, device=device) * 0.05).bfloat16()
+    desc = B.make_desc(1, H, F, E, k, 0, 1, "bf16")
+    pgu, pdn = torch.empty_like(gu), torch.empty_like(dn)
+    B.easybalance_pack_weights(desc, B.EB_WEIGHTS_GATE_UP, E, gu, pgu)
+    B.easybalance_pack_weights(desc, B.EB_WEIGHTS_DOWN, E, dn, pdn)
+    a = torch.randn(2 * T, H, generator=g, device=device).bfloat16()
+    idx = torch.ones(2 * T, k, dtype=torch.int32, device=device)
+    w = torch.ones(2 * T, k, device=device)
+    P = 2 * T * k
+    o = torch.zeros(P, H, dtype=torch.bfloat16, device=device)
+    a_perm = torch.zeros(P, H, dtype=torch.bfloat16, device=device)  # rows no pair fills stay zero
+    h = torch.empty(P, F, dtype=torch.bfloat16, device=device)
+    inv = torch.empty(P, dtype=torch.int32, device=device)
+    wsb = B.easybalance_moe_step_workspace_size(desc, [T, T])
+    ws = torch.empty(wsb + 256, dtype=torch.uint8, device=device)
+    run = B.work_array([(i, 0, T, a[i * T:], idx, w) for i in range(2)])
+    B.easybalance_moe_step(desc, run, 2, [pgu], [pdn], ws.data_ptr() + (-ws.data_ptr()) % 256, wsb, o, inv,
+                           dict(a_perm=a_perm, h=h))
+    torch.cuda.synchronize()
+    z = a.double() @ gu[1].double().t()
+    hr = (torch.nn.functional.silu(z[:, :F]) * z[:, F:]).bfloat16().double()
+    ref = hr @ dn[1].double().t()
+    pos = inv.reshape(2 * T, k).long()
+    assert int(pos.max()) >= 64                      # past the rows a decode launch is sized for
+    for r in range(k):
+        assert_close(o[pos[:, r]].float().cpu().numpy(), ref.float().cpu().numpy(), "bf16", f"slot {r}")
+
+
+def test_bf16_decode_rows_do_not_depend_on_the_launch(device):
+    """The same tokens alone (a decode launch) and next to 300 others (tiles): the same bits."""
+    H, F = 512, 8192
+    log("bf16 decode launch against tiles")
+    (o1, h1, _), _ = _step(device, "bf16", H, F, 2, 0, [20], [1])
+    (o2, h2, _), _ = _step(device, "bf16", H, F, 2, 0, [20, 300], [1, 1])
+    assert torch.equal(h1.view(torch.int16), h2[:20].view(torch.int16))
+    assert torch.equal(o1.view(torch.int16), o2[:20].view(torch.int16))
+
+
 # fp32 row blocks of 16, m-tiles of 64 sharing a group's rows evenly
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 33, 48, 63, 64, 65, 127, 129, 200, 513])
 def test_f32_group_rows(rows, device):
