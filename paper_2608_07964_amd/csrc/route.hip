@@ -206,10 +206,11 @@ __device__ __forceinline__ float key_value(uint64_t key) {
 // NaN logits are left, the lowest unpicked id, so the k picks are distinct
 // experts); the softmax maximum and denominator are reduced over the 8 lanes
 // in a fixed pattern.  The picks stay in registers (k <= KMAX) and lane sub 0
-// writes idx_t and w_t once.
+// writes idx_t and w_t once (and counts the picks in hist, an LDS histogram).
 template <int PER, int KMAX>
 __device__ __forceinline__ void topk_group8(int sub, int E, int k, int norm_topk, const float* zrow,
-                                            int32_t* __restrict__ idx_t, float* __restrict__ w_t) {
+                                            int32_t* __restrict__ idx_t, float* __restrict__ w_t,
+                                            int* hist = nullptr) {
   static_assert(PER <= 32, "taken mask");
   uint64_t key[PER];
   uint32_t taken = 0;  // entries already picked
@@ -266,13 +267,21 @@ __device__ __forceinline__ void topk_group8(int sub, int E, int k, int norm_topk
       if (r < k) {
         idx_t[r] = pe[r];
         w_t[r] = pw[r] / denom;
+        if (hist) atomicAdd(&hist[pe[r]], 1);
       }
   }
 }
 
 // Expert counts of a micro-batch from its picks, one workgroup per batch entry
 // (an LDS histogram, then one plain store per expert: nothing to clear
-// beforehand; an entry without tokens gets zeros).
+// beforehand; an entry without tokens gets zeros).  Bound by the latency of
+// the picks' loads and by LDS atomics on the hot experts, so eight loads of a
+// thread are in flight together and eight copies of the histogram, in banks
+// of their own, share the hits: 32768 picks of 256 skewed experts took 10 us
+// with one copy and one load at a time.
+constexpr int kCountCopies = 8, kCountLoads = 8;
+constexpr int kCountStride = 1024 + 64 / kCountCopies;
+
 template <class RBA>
 __global__ __launch_bounds__(1024) void counts_kernel(RBA rba, int k, int E) {
   const RouteBatch& rb = rba.get();
@@ -281,12 +290,28 @@ __global__ __launch_bounds__(1024) void counts_kernel(RBA rba, int k, int E) {
   const int n = (rb.tok0[ei + 1] - rb.tok0[ei]) * k;
   const int32_t* __restrict__ idx = in_global(rb.e[ei].idx);
   int32_t* __restrict__ counts = in_global(rb.e[ei].counts);
-  __shared__ int hist[1024];
-  for (int e = threadIdx.x; e < E; e += blockDim.x) hist[e] = 0;
+  __shared__ int hist[kCountCopies * kCountStride];
+  for (int i = threadIdx.x; i < kCountCopies * E; i += blockDim.x) hist[(i / E) * kCountStride + i % E] = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&hist[idx[i]], 1);
+  int* mine = hist + (threadIdx.x % kCountCopies) * kCountStride;
+  for (int i0 = threadIdx.x; i0 < n; i0 += blockDim.x * kCountLoads) {
+    int e[kCountLoads];
+#pragma unroll
+    for (int j = 0; j < kCountLoads; ++j) {
+      const int i = i0 + j * (int)blockDim.x;
+      e[j] = i < n ? idx[i] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < kCountLoads; ++j)
+      if (e[j] >= 0) atomicAdd(&mine[e[j]], 1);
+  }
   __syncthreads();
-  for (int e = threadIdx.x; e < E; e += blockDim.x) counts[e] = hist[e];
+  for (int e = threadIdx.x; e < E; e += blockDim.x) {
+    int c = 0;
+#pragma unroll
+    for (int j = 0; j < kCountCopies; ++j) c += hist[j * kCountStride + e];
+    counts[e] = c;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -608,13 +633,15 @@ __global__ __launch_bounds__(256, KC == 2 ? 8 : 1) void route_token_kernel(RBA r
 // through a private LDS ring of kRouteKStages stages of 64 K columns, filled
 // by buffer loads straight into LDS (8 rows x 128 bytes, whole cache lines,
 // per load; 16-byte chunks XOR-swizzled as in the 128-token form below), so
-// the K loop needs no barrier.  Waves 1..3 leave their partials in LDS and
-// wave 0 adds them in that order, then the bias (a fixed summation order),
-// and writes the logits to z and to an LDS tile from which 8 lanes per token
-// pick its top-k; partials and tile reuse the rings.
+// the K loop needs no barrier.  The waves leave their partials in LDS and add
+// them in K order, then the bias (a fixed summation order), a quarter of the
+// tile each, and write the logits to z and to an LDS tile from which 8 lanes
+// per token pick its top-k; partials and tile reuse the rings.
 constexpr int kRouteKStages = 3;
 
-template <int NB, class RBA>
+// OWN: every entry of the batch fits one workgroup (1..32 tokens), which then
+// also writes the entry's expert counts.
+template <int NB, bool OWN, class RBA>
 __global__ __launch_bounds__(256) void route_mfma_kernel(RBA rba, int H, int E, int k,
                                                          int norm_topk) {
   constexpr int ZS = NB * 32 + 1;                 // padded LDS row of the logit tile
@@ -623,7 +650,7 @@ __global__ __launch_bounds__(256) void route_mfma_kernel(RBA rba, int H, int E, 
   constexpr int kALd = 4, kBLd = 4 * NB;          // 1 KB loads of one stage
   constexpr int kAhead = (kALd + kBLd) * (kRouteKStages - 1);
   static_assert(kAhead < 64, "vmcnt range");
-  static_assert((3 * NB * 16 * 64 + 32 * ZS) * 4 <= 4 * WRING * 2, "partials and logit tile fit in the rings");
+  static_assert((4 * NB * 16 * 64 + 32 * ZS + NB * 32) * 4 <= 4 * WRING * 2, "partials, logit tile and counts fit in the rings");
   __shared__ __attribute__((aligned(1024))) bf16_t ring[4 * WRING];
   // the rings are written by global->LDS loads the compiler does not see
   asm volatile("" ::"v"(ring) : "memory");
@@ -640,6 +667,9 @@ __global__ __launch_bounds__(256) void route_mfma_kernel(RBA rba, int H, int E, 
   float* __restrict__ z = in_global(rb.e[ei].z);
   int32_t* __restrict__ idx = in_global(rb.e[ei].idx);
   float* __restrict__ w = in_global(rb.e[ei].w);
+  float bv[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) bv[nb] = bias[min(nb * 32 + lrow, E - 1)];
   // buffer descriptors: token rows past T and router rows past E read zeros
   // (their logits are never used)
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
@@ -705,30 +735,29 @@ __global__ __launch_bounds__(256) void route_mfma_kernel(RBA rba, int H, int E, 
   __builtin_amdgcn_s_waitcnt(7 << 4);
   __syncthreads();
   float(*part)[NB][16][64] = reinterpret_cast<float(*)[NB][16][64]>(ring);
-  float(*zs)[ZS] = reinterpret_cast<float(*)[ZS]>(reinterpret_cast<float*>(ring) + 3 * NB * 16 * 64);
-  if (wave > 0) {
+  float(*zs)[ZS] = reinterpret_cast<float(*)[ZS]>(reinterpret_cast<float*>(ring) + 4 * NB * 16 * 64);
+  int* hist = reinterpret_cast<int*>(ring) + 4 * NB * 16 * 64 + 32 * ZS;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) part[wave - 1][nb][v][lane] = acc[nb][v];
-  }
+    for (int v = 0; v < 16; ++v) part[wave][nb][v][lane] = acc[nb][v];
+  if (OWN && threadIdx.x < NB * 32) hist[threadIdx.x] = 0;
   __syncthreads();
-  if (wave == 0) {
+  // wavefront q adds the four partials (in K order) of accumulators 4 q .. 4 q + 3
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
+  for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        float sum = acc[nb][v];
+    for (int j = 0; j < 4; ++j) {
+      float sum = part[0][nb][4 * wave + j][lane];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) sum += part[q][nb][v][lane];
-        // C[row][col]: col = lane % 32 of block nb (expert), row = 8 (v/4) + 4 (lane/32) + v%4 (token)
-        const int tl = 8 * (v >> 2) + 4 * khalf + (v & 3);
-        const int e = nb * 32 + lrow;
-        if (e < E) {
-          const float ze = sum + bias[e];
-          zs[tl][e] = ze;
-          if (z != nullptr && t0 + tl < T) z[(size_t)(t0 + tl) * E + e] = ze;
-        }
+      for (int q = 1; q < 4; ++q) sum += part[q][nb][4 * wave + j][lane];
+      // C[row][col]: col = lane % 32 of block nb (expert), row = 8 (v/4) + 4 (lane/32) + v%4 (token), v = 4 wave + j
+      const int tl = 8 * wave + 4 * khalf + j;
+      const int e = nb * 32 + lrow;
+      if (e < E) {
+        const float ze = sum + bv[nb];
+        zs[tl][e] = ze;
+        if (z != nullptr && t0 + tl < T) z[(size_t)(t0 + tl) * E + e] = ze;
       }
     }
   }
@@ -738,49 +767,70 @@ __global__ __launch_bounds__(256) void route_mfma_kernel(RBA rba, int H, int E, 
   if (t < T) {
     if (k <= 8)
       topk_group8<NB * 4, 8>(threadIdx.x & 7, E, k, norm_topk, zs[tl], idx + (size_t)t * k,
-                             w + (size_t)t * k);
+                             w + (size_t)t * k, OWN ? hist : nullptr);
     else
       topk_group8<NB * 4, 16>(threadIdx.x & 7, E, k, norm_topk, zs[tl], idx + (size_t)t * k,
-                              w + (size_t)t * k);
+                              w + (size_t)t * k, OWN ? hist : nullptr);
+  }
+  if constexpr (OWN) {
+    __syncthreads();
+    int32_t* __restrict__ counts = in_global(rb.e[ei].counts);
+    if ((int)threadIdx.x < E) counts[threadIdx.x] = hist[threadIdx.x];
   }
 }
 
 // ---------------------------------------------------------------------------
-// Router logits for E > 64 experts (bf16): 128 tokens per workgroup of 8
-// wavefronts, wavefront w taking tokens 64 (w / 4) .. + 63 and the NBW
-// 32-expert blocks from NBW (w % 4) on, every wavefront over the whole of K.
-// Workgroups take the batch's 128-token tiles in order (entry by entry, from
-// the batch's 32-token block table), so consecutive tiles run on different
-// XCDs.  K advances 64 columns at a time through an
-// LDS ring of kRouteStages stages filled by buffer loads straight into LDS:
-// 1 KB per load is 8 rows x 128 bytes, whole cache lines, and each row's
-// 16-byte chunk c sits at c ^ ((row >> 1) & 7) so the fragment reads are
-// conflict-free.  Every logit is one chain of MFMAs over K in ascending order
-// plus the bias, so it does not depend on the token's block or batch.  The
-// logit tile for the top-k reuses the ring once the K loop is done.
-constexpr int kRouteStages = 3;
-constexpr int kRouteTokens = 128;
+// Router logits for E > 64 experts (bf16): TOK tokens (32 MBW WM) per
+// workgroup of WM x WN wavefronts, wavefront w taking tokens
+// 32 MBW (w / WN) .. + 32 MBW - 1 and the NBW 32-expert blocks from
+// NBW (w % WN) on, every wavefront over the whole of K.  K advances 64
+// columns at a time through an LDS ring of ST stages filled by buffer loads
+// straight into LDS: 1 KB per load is 8 rows x 128 bytes, whole cache lines,
+// and each row's 16-byte chunk c sits at c ^ ((row >> 1) & 7) so the fragment
+// reads are conflict-free.  Every logit is one chain of MFMAs over K in
+// ascending order plus the bias, so it does not depend on the tile, the
+// token's block or the batch.  The logit tile for the top-k reuses the ring
+// once the K loop is done.
+//
+// Each workgroup streams every router row (3.7 MB at H = 7168, E = 256), so
+// 128-token tiles read the least, but they are few: see kRouteWideTokens.
+template <int NBW_, int MBW_, int WM_, int WN_, int ST_>
+struct RouteTile {
+  static constexpr int NBW = NBW_, MBW = MBW_, WM = WM_, WN = WN_, ST = ST_, WAVES = WM * WN;
+  static constexpr int NB = WN * NBW;               // 32-expert blocks of the workgroup
+  static constexpr int TOK = 32 * MBW * WM;
+  static constexpr int A_ELEMS = TOK * 64, B_ELEMS = NB * 32 * 64;  // one stage of the token / router rows
+  static constexpr int RING = ST * (A_ELEMS + B_ELEMS);
+  static constexpr int ZS = NB * 32 + 1;            // padded row of the logit tile (floats)
+  static constexpr int A_LOADS = (TOK / 8 + WAVES - 1) / WAVES, B_LOADS = NB * 4 / WAVES;  // 8-row loads per wavefront
+  static constexpr int A_WAVES = TOK / 8 / A_LOADS; // wavefronts that load token rows
+  static_assert(A_LOADS * A_WAVES * 8 == TOK && B_LOADS * WAVES == NB * 4, "whole loads");
+  static_assert((TOK * ZS + NB * 32) * 4 <= RING * 2 && RING * 2 <= 160 * 1024, "logit tile and counts fit in the ring");
+  static_assert((ST - 2) * (A_LOADS + B_LOADS) < 64, "vmcnt range");
+};
+using RouteTile128x128 = RouteTile<1, 2, 2, 4, 3>;  // E <= 128
+using RouteTile128x256 = RouteTile<2, 2, 2, 4, 3>;  // E <= 256
+using RouteTile32x128 = RouteTile<1, 1, 1, 4, 6>;
+using RouteTile32x256 = RouteTile<1, 1, 1, 8, 4>;
 
-template <int NBW, class RBA>
-__global__ __launch_bounds__(512) void route_lds_kernel(RBA rba, int H, int E, int k, int norm_topk) {
-  constexpr int NB = 4 * NBW;                       // 32-expert blocks of the workgroup
-  constexpr int A_ELEMS = kRouteTokens * 64;        // one stage of the token rows (16 KB)
-  constexpr int B_ELEMS = NB * 32 * 64;             // one stage of the router rows
-  constexpr int RING = kRouteStages * (A_ELEMS + B_ELEMS);
-  constexpr int ZS = NB * 32 + 1;                   // padded row of the logit tile (floats)
-  static_assert(kRouteTokens * ZS * 4 <= RING * 2, "logit tile fits in the ring");
-  __shared__ __attribute__((aligned(1024))) bf16_t ring[RING];
+// OWN: as for route_mfma_kernel.  HALF: workgroup column y takes experts
+// 32 NB y on and only writes their logits to z (topk_rows_kernel follows).
+template <class C, bool OWN, bool HALF, class RBA>
+__global__ __launch_bounds__(64 * C::WAVES) void route_lds_kernel(RBA rba, int H, int E_all, int k, int norm_topk) {
+  constexpr int NBW = C::NBW, MBW = C::MBW, ST = C::ST, ZS = C::ZS;
+  __shared__ __attribute__((aligned(1024))) bf16_t ring[C::RING];
   // the ring is written by global->LDS loads the compiler does not see
   asm volatile("" ::"v"(ring) : "memory");
   const RouteBatch& rb = rba.get();
-  // workgroup q: the q-th 128-token tile of the batch, entries in order
-  // (an entry of b 32-token blocks has ceil(b / 4) tiles)
+  // workgroup q: the q-th tile of the batch, entries in order (an entry of b
+  // 32-token blocks has ceil(32 b / TOK) tiles), so consecutive tiles run on
+  // different XCDs
   int ei = -1, t0 = 0;
   for (int i = 0, base = 0; i < rb.n; ++i) {
-    const int nt = (rb.blk0[i + 1] - rb.blk0[i] + 3) / 4;
+    const int nt = (rb.blk0[i + 1] - rb.blk0[i] + C::TOK / 32 - 1) / (C::TOK / 32);
     if ((int)blockIdx.x < base + nt) {
       ei = i;
-      t0 = ((int)blockIdx.x - base) * kRouteTokens;
+      t0 = ((int)blockIdx.x - base) * C::TOK;
       break;
     }
     base += nt;
@@ -788,17 +838,22 @@ __global__ __launch_bounds__(512) void route_lds_kernel(RBA rba, int H, int E, i
   if (ei < 0) return;  // past the live tiles
   const int T = rb.tok0[ei + 1] - rb.tok0[ei];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave / C::WN, wn = wave % C::WN;
   const int lrow = lane & 31, khalf = lane >> 5;
   const bf16_t* __restrict__ a = in_global(static_cast<const bf16_t*>(rb.e[ei].a));
-  const bf16_t* __restrict__ Wg = in_global(static_cast<const bf16_t*>(rb.e[ei].Wg));
-  const float* __restrict__ bias = in_global(rb.e[ei].bias);
+  const int e_first = HALF ? (int)blockIdx.y * (C::NB * 32) : 0;
+  const int E = HALF ? min(E_all - e_first, C::NB * 32) : E_all;  // experts of this workgroup
+  const bf16_t* __restrict__ Wg = in_global(static_cast<const bf16_t*>(rb.e[ei].Wg)) + (size_t)e_first * H;
+  const float* __restrict__ bias = in_global(rb.e[ei].bias) + e_first;
   float* __restrict__ z = in_global(rb.e[ei].z);
   int32_t* __restrict__ idx = in_global(rb.e[ei].idx);
   float* __restrict__ w = in_global(rb.e[ei].w);
+  float bv[NBW];
+#pragma unroll
+  for (int nb = 0; nb < NBW; ++nb) bv[nb] = bias[min(32 * (NBW * wn + nb) + lrow, E - 1)];
   // buffer descriptors: rows past the tokens' or the experts' end read zeros
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<bf16_t*>(a + (size_t)t0 * H), (short)0, min(T - t0, kRouteTokens) * H * 2, 0x00020000);
+      const_cast<bf16_t*>(a + (size_t)t0 * H), (short)0, min(T - t0, C::TOK) * H * 2, 0x00020000);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t*>(Wg), (short)0, (int)(E * H * 2), 0x00020000);
   // load lane l: row l / 8 of an 8-row block, physical chunk l % 8 holding
@@ -808,66 +863,67 @@ __global__ __launch_bounds__(512) void route_lds_kernel(RBA rba, int H, int E, i
   const int c_even = lp ^ ((lr >> 1) & 7), c_odd = c_even ^ 4;
   const int row_b = 2 * H;                // bytes of one row
   const int voff_even = lr * row_b + c_even * 16, voff_odd = lr * row_b + c_odd * 16;
-  // wave w loads token rows 16 w + 8 j (j < 2) and router rows 4 NB w + 8 j
-  // (j < NB / 2); block parity j & 1 in both
-  constexpr int kALoads = kRouteTokens / 8 / 8, kBLoads = NB * 32 / 8 / 8;
   const int nst = H / 64;
   auto issue = [&](int st, int slot) {
     st = min(st, nst - 1);  // past the last stage: reload it into a slot nobody reads
-    bf16_t* sa = ring + slot * (A_ELEMS + B_ELEMS);
-    bf16_t* sb = sa + A_ELEMS;
+    bf16_t* sa = ring + slot * (C::A_ELEMS + C::B_ELEMS);
+    bf16_t* sb = sa + C::A_ELEMS;
+    if (wave < C::A_WAVES) {
 #pragma unroll
-    for (int j = 0; j < kALoads; ++j) {
-      const int r0 = kALoads * 8 * wave + 8 * j;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, sa + r0 * 64, 16, (j & 1) ? voff_odd : voff_even,
-                                               r0 * row_b + st * 128, 0, 0);
+      for (int j = 0; j < C::A_LOADS; ++j) {
+        const int blk = C::A_LOADS * wave + j;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, sa + blk * 8 * 64, 16, (blk & 1) ? voff_odd : voff_even,
+                                                 blk * 8 * row_b + st * 128, 0, 0);
+      }
     }
 #pragma unroll
-    for (int j = 0; j < kBLoads; ++j) {
-      const int r0 = kBLoads * 8 * wave + 8 * j;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, sb + r0 * 64, 16, (j & 1) ? voff_odd : voff_even,
-                                               r0 * row_b + st * 128, 0, 0);
+    for (int j = 0; j < C::B_LOADS; ++j) {
+      const int blk = C::B_LOADS * wave + j;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, sb + blk * 8 * 64, 16, (blk & 1) ? voff_odd : voff_even,
+                                               blk * 8 * row_b + st * 128, 0, 0);
     }
   };
-  constexpr int kLoadsPerStage = kALoads + kBLoads;  // this wavefront's loads of one stage
-  constexpr int kWaitAhead = kLoadsPerStage * (kRouteStages - 2);
-  static_assert(kWaitAhead < 64, "vmcnt range");
-  floatx16_t acc[2][NBW];
+  floatx16_t acc[MBW][NBW];
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+  for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
     for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
   const int sw = (lrow >> 1) & 7;
 #pragma unroll
-  for (int s = 0; s < kRouteStages - 1; ++s) issue(s, s);
+  for (int s = 0; s < ST - 1; ++s) issue(s, s);
+  int slot = 0;
   for (int s = 0; s < nst; ++s) {
     // stage s has landed once only the later stages' loads are in flight, and
     // this wave's fragment reads of stage s-1 are done (lgkmcnt 0) before the
     // barrier lets another wave refill that slot
+    constexpr int kA = (ST - 2) * (C::A_LOADS + C::B_LOADS), kB = (ST - 2) * C::B_LOADS;
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((kWaitAhead & 15) | ((kWaitAhead >> 4) << 14) | (7 << 4));
+    if (wave < C::A_WAVES)
+      __builtin_amdgcn_s_waitcnt((kA & 15) | ((kA >> 4) << 14) | (7 << 4));
+    else
+      __builtin_amdgcn_s_waitcnt((kB & 15) | ((kB >> 4) << 14) | (7 << 4));
     __builtin_amdgcn_s_barrier();  // every wave's part of stage s is in LDS; stage s-1 is read
     asm volatile("" ::: "memory");
-    const int slot = s % kRouteStages;
-    issue(s + kRouteStages - 1, (s + kRouteStages - 1) % kRouteStages);
-    const bf16_t* sa = ring + slot * (A_ELEMS + B_ELEMS) + (64 * wm) * 64;
-    const bf16_t* sb = ring + slot * (A_ELEMS + B_ELEMS) + A_ELEMS + (32 * NBW * wn) * 64;
+    issue(s + ST - 1, slot == 0 ? ST - 1 : slot - 1);
+    const bf16_t* sa = ring + slot * (C::A_ELEMS + C::B_ELEMS) + (32 * MBW * wm) * 64;
+    const bf16_t* sb = ring + slot * (C::A_ELEMS + C::B_ELEMS) + C::A_ELEMS + (32 * NBW * wn) * 64;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const int ch = ((2 * ks + khalf) ^ sw) * 8;
-      bf16x8_t af[2], bfr[NBW];
+      bf16x8_t af[MBW], bfr[NBW];
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb) af[mb] = *reinterpret_cast<const bf16x8_t*>(sa + (mb * 32 + lrow) * 64 + ch);
+      for (int mb = 0; mb < MBW; ++mb) af[mb] = *reinterpret_cast<const bf16x8_t*>(sa + (mb * 32 + lrow) * 64 + ch);
 #pragma unroll
       for (int nb = 0; nb < NBW; ++nb) bfr[nb] = *reinterpret_cast<const bf16x8_t*>(sb + (nb * 32 + lrow) * 64 + ch);
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NBW; ++nb)
           acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[mb], bfr[nb], acc[mb][nb], 0, 0, 0);
     }
+    slot = slot == ST - 1 ? 0 : slot + 1;
   }
   // every load (including those past the last stage) has landed and every
   // wave is done reading the ring before the logit tile overwrites it
@@ -875,38 +931,80 @@ __global__ __launch_bounds__(512) void route_lds_kernel(RBA rba, int H, int E, i
   __builtin_amdgcn_s_waitcnt(7 << 4);
   __syncthreads();
   float* zs = reinterpret_cast<float*>(ring);
+  int* hist = reinterpret_cast<int*>(ring) + C::TOK * ZS;
   // acc[mb][nb][v]: expert 32 (NBW wn + nb) + lane % 32, token
-  // 64 wm + 32 mb + 8 (v / 4) + 4 (lane / 32) + v % 4
+  // 32 (MBW wm + mb) + 8 (v / 4) + 4 (lane / 32) + v % 4
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
+  for (int mb = 0; mb < MBW; ++mb) {
 #pragma unroll
     for (int nb = 0; nb < NBW; ++nb) {
       const int e = 32 * (NBW * wn + nb) + lrow;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int tl = 64 * wm + 32 * mb + 8 * (v >> 2) + 4 * khalf + (v & 3);
+        const int tl = 32 * (MBW * wm + mb) + 8 * (v >> 2) + 4 * khalf + (v & 3);
         if (e < E) {
-          const float ze = acc[mb][nb][v] + bias[e];
-          zs[tl * ZS + e] = ze;
-          if (z != nullptr && t0 + tl < T) z[(size_t)(t0 + tl) * E + e] = ze;
+          const float ze = acc[mb][nb][v] + bv[nb];
+          if (!HALF) zs[tl * ZS + e] = ze;
+          if (z != nullptr && t0 + tl < T) z[(size_t)(t0 + tl) * E_all + e_first + e] = ze;
         }
       }
     }
   }
+  if constexpr (HALF) return;
+  if constexpr (OWN)
+    for (int e = threadIdx.x; e < E; e += 64 * C::WAVES) hist[e] = 0;
   __syncthreads();
-  // 8 lanes per token, two tokens per group of 8 lanes
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int tl = (threadIdx.x >> 3) + 64 * half, t = t0 + tl;
+  // 8 lanes per token
+  for (int tl = threadIdx.x >> 3; tl < C::TOK; tl += 8 * C::WAVES) {
+    const int t = t0 + tl;
     if (t < T) {
       if (k <= 8)
-        topk_group8<NB * 4, 8>(threadIdx.x & 7, E, k, norm_topk, zs + tl * ZS, idx + (size_t)t * k,
-                               w + (size_t)t * k);
+        topk_group8<C::NB * 4, 8>(threadIdx.x & 7, E, k, norm_topk, zs + tl * ZS, idx + (size_t)t * k,
+                                  w + (size_t)t * k, OWN ? hist : nullptr);
       else
-        topk_group8<NB * 4, 16>(threadIdx.x & 7, E, k, norm_topk, zs + tl * ZS, idx + (size_t)t * k,
-                                w + (size_t)t * k);
+        topk_group8<C::NB * 4, 16>(threadIdx.x & 7, E, k, norm_topk, zs + tl * ZS, idx + (size_t)t * k,
+                                   w + (size_t)t * k, OWN ? hist : nullptr);
     }
   }
+  if constexpr (OWN) {
+    __syncthreads();
+    int32_t* __restrict__ counts = in_global(rb.e[ei].counts);
+    for (int e = threadIdx.x; e < E; e += 64 * C::WAVES) counts[e] = hist[e];
+  }
+}
+
+// Top-k of 32 tokens per workgroup from the logits route_lds_kernel<HALF>
+// wrote: the rows go through LDS by whole lines, 8 lanes per token pick.
+template <int NB, class RBA>
+__global__ __launch_bounds__(256) void topk_rows_kernel(RBA rba, int E, int k, int norm_topk) {
+  constexpr int ZS = NB * 32 + 1;
+  __shared__ float zs[32 * ZS];
+  const RouteBatch& rb = rba.get();
+  if ((int)blockIdx.x >= rb.blk0[rb.n]) return;  // past the live 32-token blocks
+  const int ei = find_entry(rb.blk0, rb.n, blockIdx.x);
+  const int T = rb.tok0[ei + 1] - rb.tok0[ei];
+  const int t0 = (blockIdx.x - rb.blk0[ei]) * 32;
+  const float* __restrict__ z = in_global(rb.e[ei].z) + (size_t)t0 * E;
+  const int rows = min(T - t0, 32), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float v[8][NB / 2];  // wavefront w: rows w, w + 4, ..; 64 logits per load, all loads in flight
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+#pragma unroll
+    for (int j = 0; j < NB / 2; ++j)
+      v[r][j] = z[(size_t)min(wave + 4 * r, rows - 1) * E + min(lane + 64 * j, E - 1)];
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+#pragma unroll
+    for (int j = 0; j < NB / 2; ++j) zs[(wave + 4 * r) * ZS + lane + 64 * j] = v[r][j];
+  __syncthreads();
+  const int tl = threadIdx.x >> 3, t = t0 + tl;
+  if (t >= T) return;
+  int32_t* idx_t = in_global(rb.e[ei].idx) + (size_t)t * k;
+  float* w_t = in_global(rb.e[ei].w) + (size_t)t * k;
+  if (k <= 8)
+    topk_group8<NB * 4, 8>(threadIdx.x & 7, E, k, norm_topk, zs + tl * ZS, idx_t, w_t);
+  else
+    topk_group8<NB * 4, 16>(threadIdx.x & 7, E, k, norm_topk, zs + tl * ZS, idx_t, w_t);
 }
 
 // ---------------------------------------------------------------------------
@@ -922,6 +1020,18 @@ __global__ __launch_bounds__(256) void topk_kernel(int T, int E, int k, int norm
   topk_token(E, k, norm_topk, [&](int e) { return zr[e]; }, idx + (size_t)t * k, w + (size_t)t * k);
 }
 
+// Tiles of the routers for more than 64 experts.  A workgroup pulls its rows
+// at 50-55 GB/s whatever the tile, so what counts is how many workgroups share
+// the reading of the router rows: above 8192 tokens (more than one 32-token
+// tile per CU) 128-token tiles, which read each router row a quarter as often
+// (H = 7168, E = 256: 8192 tokens 99 us in 32-token and 145 in 128-token
+// tiles, 16384 tokens 184 and 153, 4096 tokens 89 and 132).
+constexpr int kRouteWideTokens = 8192;
+// Up to 4096 tokens (half a tile per CU) with more than 128 experts, two
+// workgroups per 32-token tile take half the experts each, and a second launch
+// picks the top-k from the stored logits.
+constexpr int kRouteHalvesTokens = 4096;
+
 // Whether the routing of a batch runs in a fixed set of launches (no launch
 // per entry): every bf16 stack, and fp32 stacks on the fused per-token path.
 template <typename TA>
@@ -929,13 +1039,34 @@ bool fused_token_path(const eb_model_desc& d) {
   return (sizeof(TA) == 2 ? d.E <= 8 : d.E <= 64) && d.H <= kTokMaxH;
 }
 
+template <bool OWN, class RBA>
+void route_mfma_launch(const eb_model_desc& d, RBA rba, int grid, hipStream_t s) {
+  hipLaunchKernelGGL((route_mfma_kernel<2, OWN, RBA>), dim3(grid), dim3(256), 0, s, rba, d.H, d.E, d.k, d.norm_topk);
+}
+template <class C, bool OWN, class RBA>
+void route_lds_launch(const eb_model_desc& d, RBA rba, int grid, hipStream_t s) {
+  hipLaunchKernelGGL((route_lds_kernel<C, OWN, false, RBA>), dim3(grid), dim3(64 * C::WAVES), 0, s, rba, d.H, d.E,
+                     d.k, d.norm_topk);
+}
+template <class RBA>
+void route_halves_launch(const eb_model_desc& d, RBA rba, int grid, hipStream_t s) {
+  hipLaunchKernelGGL((route_lds_kernel<RouteTile32x128, false, true, RBA>), dim3(grid, 2),
+                     dim3(64 * RouteTile32x128::WAVES), 0, s, rba, d.H, d.E, d.k, d.norm_topk);
+  hipLaunchKernelGGL((topk_rows_kernel<8, RBA>), dim3(grid), dim3(256), 0, s, rba, d.E, d.k, d.norm_topk);
+}
+
 // grid_entries / grid_tokens / grid_blocks: entries, tokens and 32-token
 // blocks the grids cover (the live batch's, or a full batch's when the table
-// is in device memory); host_rb: the table itself when the host built it
+// is in device memory); one_block: every entry has 1 to 32 tokens;
+// z_stored: no entry's z is NULL; host_rb: the table itself when the host built it
 // (the fp32 per-entry path needs it).
 template <typename TA, class RBA>
 hipError_t route_batch_typed(const eb_model_desc& d, RBA rba, const RouteBatch* host_rb, int grid_entries,
-                             int grid_tokens, int grid_blocks, hipStream_t s) {
+                             int grid_tokens, int grid_blocks, bool one_block, bool z_stored, hipStream_t s) {
+  // the matrix-core routers count an entry's picks themselves where one
+  // workgroup holds the whole entry
+  const bool halves = z_stored && d.E > 128 && grid_tokens <= kRouteHalvesTokens;
+  const bool own = !halves && sizeof(TA) == 2 && one_block && !fused_token_path<TA>(d) && grid_tokens <= kRouteWideTokens;
   if (grid_tokens > 0) {
     if (fused_token_path<TA>(d)) {
       prof_start(EB_K_ROUTE_LOGITS, s);
@@ -966,18 +1097,21 @@ hipError_t route_batch_typed(const eb_model_desc& d, RBA rba, const RouteBatch* 
       prof_stop(EB_K_ROUTE_NORM, s);
       prof_start(EB_K_ROUTE_LOGITS, s);
       if (sizeof(TA) == 2) {
-        const dim3 grid(grid_blocks);
-        // 128-token tiles: at most a quarter of the blocks plus one per entry
-        const dim3 grid_tiles((grid_blocks + 3) / 4 + grid_entries);
         const int nb = (d.E + 31) / 32;
         if (nb <= 2)
-          hipLaunchKernelGGL((route_mfma_kernel<2, RBA>), grid, dim3(256), 0, s, rba, d.H, d.E, d.k, d.norm_topk);
+          own ? route_mfma_launch<true>(d, rba, grid_blocks, s) : route_mfma_launch<false>(d, rba, grid_blocks, s);
+        else if (grid_tokens > kRouteWideTokens)
+          // 128-token tiles: at most a quarter of the blocks plus one per entry
+          nb <= 4 ? route_lds_launch<RouteTile128x128, false>(d, rba, (grid_blocks + 3) / 4 + grid_entries, s)
+                  : route_lds_launch<RouteTile128x256, false>(d, rba, (grid_blocks + 3) / 4 + grid_entries, s);
         else if (nb <= 4)
-          hipLaunchKernelGGL((route_lds_kernel<1, RBA>), grid_tiles, dim3(512), 0, s, rba, d.H, d.E, d.k,
-                             d.norm_topk);
+          own ? route_lds_launch<RouteTile32x128, true>(d, rba, grid_blocks, s)
+              : route_lds_launch<RouteTile32x128, false>(d, rba, grid_blocks, s);
+        else if (halves)
+          route_halves_launch(d, rba, grid_blocks, s);
         else
-          hipLaunchKernelGGL((route_lds_kernel<2, RBA>), grid_tiles, dim3(512), 0, s, rba, d.H, d.E, d.k,
-                             d.norm_topk);
+          own ? route_lds_launch<RouteTile32x256, true>(d, rba, grid_blocks, s)
+              : route_lds_launch<RouteTile32x256, false>(d, rba, grid_blocks, s);
         prof_stop(EB_K_ROUTE_LOGITS, s);
       } else {
         if (host_rb == nullptr) return hipErrorInvalidValue;
@@ -1004,7 +1138,7 @@ hipError_t route_batch_typed(const eb_model_desc& d, RBA rba, const RouteBatch* 
     }
   }
   prof_start(EB_K_ROUTE_TOPK, s);
-  if (grid_entries > 0)
+  if (grid_entries > 0 && !own)
     hipLaunchKernelGGL((counts_kernel<RBA>), dim3(grid_entries), dim3(1024), 0, s, rba, d.k, d.E);
   prof_stop(EB_K_ROUTE_TOPK, s);
   return hipGetLastError();
@@ -1014,9 +1148,14 @@ hipError_t route_batch_typed(const eb_model_desc& d, RBA rba, const RouteBatch* 
 
 hipError_t launch_route_batch(const eb_model_desc& d, const RouteBatch& rb, hipStream_t s) {
   const ByValue<RouteBatch> a{rb};
+  bool one = true, z = true;
+  for (int i = 0; i < rb.n; ++i) {
+    one = one && rb.blk0[i + 1] - rb.blk0[i] == 1;
+    z = z && rb.e[i].z != nullptr;
+  }
   if (d.dtype == EB_DTYPE_BF16)
-    return route_batch_typed<bf16_t>(d, a, &rb, rb.n, rb.tok0[rb.n], rb.blk0[rb.n], s);
-  return route_batch_typed<float>(d, a, &rb, rb.n, rb.tok0[rb.n], rb.blk0[rb.n], s);
+    return route_batch_typed<bf16_t>(d, a, &rb, rb.n, rb.tok0[rb.n], rb.blk0[rb.n], one, z, s);
+  return route_batch_typed<float>(d, a, &rb, rb.n, rb.tok0[rb.n], rb.blk0[rb.n], one, z, s);
 }
 
 bool route_logits_required(const eb_model_desc& d) {
@@ -1032,8 +1171,9 @@ hipError_t launch_route_batch_dev(const eb_model_desc& d, const RouteBatch* rb, 
   if (!route_batch_device_ok(d) || max_entries > kRouteBatch) return hipErrorInvalidValue;
   const InMemory<RouteBatch> a{rb};
   const int tokens = max_entries * T, blocks = max_entries * ((T + 31) / 32);
-  if (d.dtype == EB_DTYPE_BF16) return route_batch_typed<bf16_t>(d, a, nullptr, max_entries, tokens, blocks, s);
-  return route_batch_typed<float>(d, a, nullptr, max_entries, tokens, blocks, s);
+  const bool one = T >= 1 && T <= 32;
+  if (d.dtype == EB_DTYPE_BF16) return route_batch_typed<bf16_t>(d, a, nullptr, max_entries, tokens, blocks, one, true, s);
+  return route_batch_typed<float>(d, a, nullptr, max_entries, tokens, blocks, one, true, s);
 }
 
 hipError_t launch_route(const eb_model_desc& d, int T, const float* x, const float* gain,
