@@ -109,6 +109,23 @@ __device__ __forceinline__ void bar() {
   asm volatile("" ::: "memory");
 }
 
+// Barrier that orders LDS accesses only: a wave's LDS reads and writes are done
+// when it arrives, its global stores need not be (__syncthreads would wait for
+// an item's output stores, 3 to 6 us with every CU storing).
+__device__ __forceinline__ void bar_lds() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+  bar();
+}
+
+// A wavefront-uniform pointer the compiler cannot prove uniform, in scalar
+// registers (a buffer descriptor in vector registers costs a loop per load).
+__device__ __forceinline__ const bf16_t* uniform(const bf16_t* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (const bf16_t*)(((uint64_t)hi << 32) | lo);
+}
+
 // Raw buffer descriptor over [base, base + bytes) (bytes < 2^32); offsets
 // past the end read zeros.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, uint32_t bytes) {
@@ -392,42 +409,60 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 // nb + NB/2 the up rows of the same f; h = bf16(SwiGLU(gate, up)).  Down:
 // o = bf16(acc).  Blocks past nact were not computed (and may be another
 // wavefront row's rows).
+//
+// The wavefront's tile goes through its own part of the LDS ring (free once
+// every wavefront has left the K loop) so that each store instruction writes
+// whole 128-byte (down) or 64-byte (gate/up) runs of a row; stored from the
+// accumulators it would write 16 bytes of each of 32 rows.  Rows hold 16-byte
+// chunks, XOR-swizzled by row against bank conflicts.  An item's time
+// outside its K loop (2048-row groups, K = 1408, 256 columns: epilogue 4.1,
+// then 5.7 us until the next item starts, beside 30 us of K loop) fell to 1.9
+// and 1.8 us, with bar_lds instead of a barrier that waits for the stores.
 template <class C, int MODE>
 __device__ __forceinline__ void epilogue_tr(const GroupedProblem& p, const floatx16 (&acc)[C::MB][C::NB],
-                                            bf16_t* C_out, int row0, int row_end, int ni, int r0w, int wn,
-                                            int nact, int lrow, int khalf) {
+                                            bf16_t* smem, bf16_t* C_out, int row0, int row_end, int ni, int r0w,
+                                            int wave, int wn, int nact, int lane) {
+  constexpr int COLS = MODE == MODE_GATEUP ? C::TN / 2 : C::TN;  // output columns of the wavefront
+  constexpr int CH = COLS / 8, ROWS = 64 / CH;                   // chunks of a row; rows of one store
+  const int N = MODE == MODE_GATEUP ? p.F : p.H;
+  const int lrow = lane & 31, khalf = lane >> 5;
+  bf16_t* st = smem + wave * (C::TM * C::TN);
+  auto chunk = [](int r, int c) { return c ^ (CH == 8 ? (r >> 1) & 7 : (r >> 2) & 3); };
 #pragma unroll
   for (int mb = 0; mb < C::MB; ++mb) {
-    const int row = row0 + r0w + mb * 32 + lrow;
-    if (mb >= nact || row >= row_end) continue;
-    if constexpr (MODE == MODE_GATEUP) {
+    if (mb >= nact) continue;
+    const int r = mb * 32 + lrow;
 #pragma unroll
-      for (int nb = 0; nb < C::NB / 2; ++nb) {
-        const floatx16& gt = acc[mb][nb];
-        const floatx16& up = acc[mb][nb + C::NB / 2];
+    for (int nb = 0; nb < COLS / 32; ++nb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int f = ni * (BN / 2) + wn * (C::TN / 2) + nb * 32 + 8 * g + 4 * khalf;
-          uint2 v;
+      for (int g = 0; g < 4; ++g) {
+        uint2 v;
+        if constexpr (MODE == MODE_GATEUP) {
+          const floatx16 &gt = acc[mb][nb], &up = acc[mb][nb + C::NB / 2];
           v.x = pack_bf16x2(swiglu(gt[4 * g], up[4 * g]), swiglu(gt[4 * g + 1], up[4 * g + 1]));
           v.y = pack_bf16x2(swiglu(gt[4 * g + 2], up[4 * g + 2]), swiglu(gt[4 * g + 3], up[4 * g + 3]));
-          *reinterpret_cast<uint2*>(C_out + (size_t)row * p.F + f) = v;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) {
-        const floatx16& c = acc[mb][nb];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int n = ni * BN + wn * C::TN + nb * 32 + 8 * g + 4 * khalf;
-          uint2 v;
+        } else {
+          const floatx16& c = acc[mb][nb];
           v.x = pack_bf16x2(c[4 * g], c[4 * g + 1]);
           v.y = pack_bf16x2(c[4 * g + 2], c[4 * g + 3]);
-          *reinterpret_cast<uint2*>(C_out + (size_t)row * p.H + n) = v;
         }
+        *reinterpret_cast<uint2*>(st + r * COLS + chunk(r, nb * 4 + g) * 8 + khalf * 4) = v;
       }
+  }
+  asm volatile("" ::: "memory");  // the reads below are of the bytes written above, as another type
+  // rows past the group's end are past the descriptor's end: not stored
+  const int rows = max(0, min(nact * 32, row_end - row0 - r0w));
+  const __amdgpu_buffer_rsrc_t rc = buffer_rsrc(uniform(C_out + (size_t)(row0 + r0w) * N), (uint32_t)(rows * N * 2));
+  const int rl = lane / CH, c = lane % CH;
+  int off = (rl * N + ni * (4 * COLS) + wn * COLS + c * 8) * 2;
+#pragma unroll
+  for (int i = 0; i < C::TM / ROWS; ++i) {
+    if (i * ROWS < nact * 32) {
+      const int r = i * ROWS + rl;
+      typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+      __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(st + r * COLS + chunk(r, c) * 8), rc, off, 0, 0);
     }
+    off += ROWS * N * 2;
   }
 }
 
@@ -491,11 +526,11 @@ __device__ __forceinline__ void run_item(const GroupedProblem& p, bf16_t* smem, 
   // whole 128-byte line)
   if (MODE == MODE_GATEUP || part == nullptr) {
     k_loop_nact<C, true>(kl, acc, nact);
-    __syncthreads();  // every wave is done with the ring before the next item refills it
-    epilogue_tr<C, MODE>(p, acc, C_out, row0, row_end, ni, wm * tm, wn, nact, lrow, khalf);
+    bar_lds();  // every wave is done with the ring before it is written again
+    epilogue_tr<C, MODE>(p, acc, smem, C_out, row0, row_end, ni, wm * tm, wave, wn, nact, lane);
   } else if constexpr (MODE == MODE_DOWN) {
     k_loop_nact<C, false>(kl, acc, nact);
-    __syncthreads();
+    bar_lds();
     // acc[mb][nb][v]: output column wn*TN + nb*32 + lrow of token row
     // wm*tm + mb*32 + 8 (v / 4) + 4 khalf + v % 4
 #pragma unroll
@@ -535,20 +570,6 @@ __device__ __forceinline__ void run_item(const GroupedProblem& p, bf16_t* smem, 
 // the 32 items one XCD runs at a time then spans 4 m-tiles x 8 n-tiles, so
 // it streams 4 activation and 8 weight tiles instead of 32 and 1.
 constexpr int kMBlock = 4;
-
-// A wavefront-uniform value the compiler cannot prove uniform, in scalar
-// registers (buffer descriptors made from vector registers cost a loop per load).
-__device__ __forceinline__ int4 uniform(int4 v) {
-  return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
-                   __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
-}
-
-// The same for a buffer descriptor's base.
-__device__ __forceinline__ const bf16_t* uniform(const bf16_t* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (const bf16_t*)(((uint64_t)hi << 32) | lo);
-}
 
 // A group record by a scalar load (i uniform): it does not queue behind the
 // vector loads in flight.  The records are written by an earlier launch.
@@ -603,8 +624,9 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
                                                                  bf16_t* __restrict__ C,
                                                                  int n_ntiles) {
   __shared__ __attribute__((aligned(1024))) bf16_t smem[kLdsElems];
-  // the next item index is broadcast through the first word of the ring,
-  // which no load writes between an item's last K stage and the next prologue
+  // the next item index is broadcast through the first word of the ring, which
+  // no load writes between an item's last K stage and the next prologue (and
+  // only wavefront 0's own output tile passes through)
   int* s_next = reinterpret_cast<int*>(smem);
   // the LDS ring is written by global->LDS loads the compiler does not see
   asm volatile("" ::"v"(smem) : "memory");
@@ -618,7 +640,7 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
 
   if (tid == 0) *s_next = q.settle(q.draw());
   __syncthreads();
-  int it = *s_next;
+  int it = __builtin_amdgcn_readfirstlane(*s_next);
   __syncthreads();
 
   while (it >= 0) {
@@ -626,7 +648,7 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
     if (tid == 0) got = q.draw();
     // group of this item: a group's items it * nsub .. (it + mt) * nsub - 1
     // cover its m-tiles it .. it + mt - 1, so item / nsub is one of them
-    const int4 gd = p.tiles[it / nsub];  // key, first row, rows, first m-tile
+    const int4 gd = scalar_record(p.tiles, it / nsub);  // key, first row, rows, first m-tile
     const int mt = (gd.z + BM - 1) / BM;
     // within the group: K part slowest, then blocks of kMBlock m-tiles, then
     // n-tile, m-tile fastest (the last block holds the mt % kMBlock rest)
@@ -652,9 +674,9 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
     else
       run_item<CfgSkinny, MODE>(p, smem, A, C, Bbase, row0, row_end, ni, K, ks0, nks, part, wave, lane);
     if (tid == 0) *s_next = q.settle(got);
-    __syncthreads();
-    it = *s_next;
-    __syncthreads();  // every thread has read it before the next prologue refills the ring
+    bar_lds();
+    it = __builtin_amdgcn_readfirstlane(*s_next);
+    bar_lds();  // every thread has read it before the next prologue refills the ring
   }
 }
 
@@ -967,7 +989,7 @@ __global__ __launch_bounds__(64 * kF32Waves, kF32Waves * kF32PerCu / 4) void gro
   while (it >= 0) {
     int got = 0;
     if (tid == 0) got = q.draw();
-    const int4 gd = uniform(p.tiles[it / n_ntiles]);  // key, first row, rows, first m-tile
+    const int4 gd = scalar_record(p.tiles, it / n_ntiles);  // key, first row, rows, first m-tile
     const int mt = (gd.z + FBM - 1) / FBM;
     const Tile2 tile = item_tile(it - gd.w * n_ntiles, mt, n_ntiles);
     // the group's m-tiles share its rows evenly in whole 16-row blocks
@@ -1038,9 +1060,9 @@ __global__ __launch_bounds__(64 * kF32Waves, kF32Waves * kF32PerCu / 4) void gro
       }
     }
     if (tid == 0) *s_next = q.settle(got);
-    __syncthreads();  // every wavefront is done with the ring; the next item is published
+    bar_lds();  // every wavefront is done with the ring; the next item is published
     it = __builtin_amdgcn_readfirstlane(*s_next);
-    __syncthreads();  // and read, before the next one overwrites it
+    bar_lds();  // and read, before the next one overwrites it
   }
 }
 
