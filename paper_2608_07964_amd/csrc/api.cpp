@@ -388,7 +388,8 @@ int moe_step_common(const eb_model_desc* desc, int32_t n_run, const eb_work* run
   const int eb = d.dtype == EB_DTYPE_BF16 ? 2 : 4;
   const StepBuffers& b = w.b;
   if ((rc = hip_status(launch_perm_count(rt, sh.n_chunks, b.hist, s), "perm_count"))) return rc;
-  if ((rc = hip_status(launch_perm_scan(rt, b.hist, b.chunk_base, b.offsets, b.tiles, gemm_bm(d.dtype), b.max_tiles, b.work_ctr, s),
+  if ((rc = hip_status(launch_perm_scan(rt, b.hist, b.chunk_base, b.offsets, b.tiles, gemm_bm(d.dtype),
+                                        gemm_tail(d.dtype, d.F), b.max_tiles, b.work_ctr, s),
                        "perm_scan")))
     return rc;
   if ((rc = hip_status(launch_perm_scatter(rt, sh.n_chunks, eb, b.chunk_base, b.perm, inv_out, b.a_perm, s),

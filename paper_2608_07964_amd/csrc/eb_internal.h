@@ -56,7 +56,8 @@ struct GroupedProblem {
                                            // (offsets[L*(E+S)])
   const int4* tiles;                       // [n_tiles] the row block's group: (key, first row,
                                            // rows, index of the group's first row block)
-  const int32_t* n_tiles;                  // device scalar: row blocks over all groups
+  const int32_t* n_tiles;                  // device [2]: row blocks over all groups, and how many
+                                           // of them come before those set aside for the end
   int32_t layer_tokens;                    // the most tokens the step has at one layer
   int32_t* work_ctr;                       // per-XCD work counters of this launch, zeroed:
                                            // XCD x's at work_ctr[x * kWorkStride]
@@ -69,9 +70,10 @@ struct GroupedProblem {
 inline int down_ksplit(int dtype, int F) { return dtype == EB_DTYPE_BF16 && F >= 8192 ? 2 : 1; }
 
 // Step counters: one 128-byte line per XCD holding its work counter of the
-// gate/up launch and (kWorkDown on) of the down launch; the number of row
-// blocks follows in the first line.
-constexpr int kWorkStride = 32, kWorkDown = 8, kWorkTiles = 16;
+// gate/up launch, that of its share of the row blocks set aside (kWorkTail
+// on) and the same two of the down launch (kWorkDown on); the numbers of row
+// blocks follow in the first line.
+constexpr int kWorkStride = 32, kWorkTail = 4, kWorkDown = 8, kWorkTiles = 16;
 constexpr int kWorkWords = 8 * kWorkStride;
 
 // Device-side entry lookup: largest rho with base[rho] <= v (bases ascending).
@@ -167,6 +169,12 @@ hipError_t launch_sched_step(const DevPassArgs& A, hipStream_t s);
 int enqueue_step_dev(const eb_model_desc& d, int N, int T, const RunTable* rt, const WeightTable& wt,
                      void* ws, void* o, int32_t* inv, hipStream_t s);
 
+// The row blocks the permutation scan sets aside at the end of the tile list:
+// the first `tiles` groups of at most `rows` rows.
+struct TailRule {
+  int32_t tiles, rows;
+};
+
 // ---- launchers (return hipError_t of the launch) ---------------------------
 hipError_t launch_route_batch(const eb_model_desc& d, const RouteBatch& rb, hipStream_t s);
 // A batch table in device memory (written by the device-side scheduler);
@@ -184,8 +192,8 @@ hipError_t launch_route(const eb_model_desc& d, int T, const float* x, const flo
 
 hipError_t launch_perm_count(const RunTable& rt, int n_chunks, int32_t* hist, hipStream_t s);
 hipError_t launch_perm_scan(const RunTable& rt, const int32_t* hist, int32_t* chunk_base,
-                            int32_t* offsets, int4* tiles, int bm, int max_tiles, int32_t* work_ctr,
-                            hipStream_t s);
+                            int32_t* offsets, int4* tiles, int bm, TailRule tail, int max_tiles,
+                            int32_t* work_ctr, hipStream_t s);
 hipError_t launch_perm_scatter(const RunTable& rt, int n_chunks, int elem_bytes,
                                const int32_t* chunk_base, int32_t* perm, int32_t* inv,
                                void* a_perm, hipStream_t s);
@@ -211,6 +219,7 @@ hipError_t launch_permute_dev(const eb_model_desc& d, const RunTable* rt, int ma
 
 // Row-block height of the grouped GEMM tiles for a dtype.
 int gemm_bm(int dtype);
+TailRule gemm_tail(int dtype, int F);
 
 // Expert weights in the layout the grouped GEMMs read (bf16: packed blocks,
 // see gemm.hip; fp32: row-major, a copy).  n matrices of N x K.

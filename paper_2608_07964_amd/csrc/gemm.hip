@@ -561,7 +561,8 @@ __device__ __forceinline__ void run_item(const GroupedProblem& p, bf16_t* smem, 
 // through that XCD's atomic counter, so items running together on one L2
 // share weight and activation tiles and no workgroup idles while its XCD has
 // work; once its XCD's range is drained it takes items from the other XCDs'
-// ranges.  Every item is taken exactly once whichever workgroup takes it.
+// ranges, then those set aside for the end (ItemQueue).  Every item is taken
+// exactly once whichever workgroup takes it.
 // The counter increment for the next item is issued at the start of the
 // current one and its result used at its end.  Each item runs in the tile
 // shape of the rows it holds; all shapes accumulate K in the same order, so a
@@ -596,25 +597,50 @@ __device__ __forceinline__ Tile2 item_tile(int local, int mt, int n_ntiles) {
 // read before it is drawn from: when every workgroup drew from all eight in
 // one line on its way out, those 2000 atomics ran one after the other for
 // about 20 us at the end of each launch.
+//
+// The list's last n_tiles[0] - n_tiles[1] row blocks are small ones the scan
+// set aside: their items are taken once the others are gone, so that the
+// launch ends on short items.  They are split into eighths like the others
+// (drawn by all XCDs from one counter, every XCD streamed from every expert:
+// a launch of 256 items of K = 7168 took 220 instead of 158 us).
 struct ItemQueue {
   int32_t* ctr;
-  long long total;
-  int xcd, victim;
-  __device__ __forceinline__ ItemQueue(const GroupedProblem& p, long long total_)
-      : ctr(p.work_ctr), total(total_), xcd(blockIdx.x % kXcds), victim(blockIdx.x % kXcds) {}
-  __device__ __forceinline__ int range_lo(int x) const { return (int)((x * total) / kXcds); }
-  __device__ __forceinline__ int draw() const { return atomicAdd(&ctr[victim * kWorkStride], 1); }
-  // item index from a value drawn from victim's counter, or -1 once every range is drained
+  long long main;  // items before the ones set aside
+  int total, xcd, victim, per_xcd;  // victim: XCD range drawn from, + kXcds for its set-aside range
+  __device__ __forceinline__ ItemQueue(const GroupedProblem& p, int nsub)
+      : ctr(p.work_ctr), main((long long)p.n_tiles[1] * nsub), total(p.n_tiles[0] * nsub), xcd(blockIdx.x % kXcds),
+        victim(blockIdx.x % kXcds), per_xcd(gridDim.x / kXcds) {}
+  __device__ __forceinline__ int bound(int x) const {  // first item of range x; bound(2 kXcds) = total
+    return x < kXcds ? (int)((x * main) / kXcds) : (int)(main + ((x - kXcds) * (total - main)) / kXcds);
+  }
+  __device__ __forceinline__ int32_t* counter() const {
+    return ctr + (victim < kXcds ? victim * kWorkStride : (victim - kXcds) * kWorkStride + kWorkTail);
+  }
+  __device__ __forceinline__ int draw() const { return atomicAdd(counter(), 1); }
+  // The first items of an XCD's range go to its workgroups by number (drawn,
+  // the first few to start would each hold a second item while others have
+  // none), the rest through its counter.
+  __device__ __forceinline__ int drawn(int got) const { return bound(victim) + got + (victim < kXcds ? per_xcd : 0); }
+  // item index from a value drawn from victim's counter, or -1 once everything
+  // is taken: the own range, the other XCDs', then the set-aside ones alike
   __device__ __forceinline__ int settle(int got) {
-    int it = range_lo(victim) + got;
-    while (it >= range_lo(victim + 1)) {
-      victim = victim + 1 == kXcds ? 0 : victim + 1;
-      if (victim == xcd) return -1;
-      it = range_lo(victim) +
-           __hip_atomic_load(&ctr[victim * kWorkStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (it < range_lo(victim + 1)) it = range_lo(victim) + draw();
+    int it = drawn(got);
+    while (it >= bound(victim + 1)) {
+      if (victim < kXcds) {
+        victim = victim + 1 == kXcds ? 0 : victim + 1;
+        if (victim == xcd) victim += kXcds;
+      } else {
+        victim = victim + 1 == 2 * kXcds ? kXcds : victim + 1;
+        if (victim == xcd + kXcds) return -1;
+      }
+      it = drawn(__hip_atomic_load(counter(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      if (it < bound(victim + 1)) it = drawn(draw());
     }
     return it;
+  }
+  __device__ __forceinline__ int first() {
+    const int it = bound(xcd) + (int)(blockIdx.x / kXcds);
+    return it < bound(xcd + 1) ? it : settle(draw());
   }
 };
 
@@ -634,11 +660,11 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ksplit = MODE == MODE_DOWN ? p.ksplit : 1;
   const int nsub = n_ntiles * ksplit;  // items per m-tile
-  ItemQueue q(p, (long long)(*p.n_tiles) * nsub);  // used by thread 0 only
+  ItemQueue q(p, nsub);  // used by thread 0 only
   const int K = MODE == MODE_GATEUP ? p.H : p.F;
   const int ES = p.E + p.S;
 
-  if (tid == 0) *s_next = q.settle(q.draw());
+  if (tid == 0) *s_next = q.first();
   __syncthreads();
   int it = __builtin_amdgcn_readfirstlane(*s_next);
   __syncthreads();
@@ -981,8 +1007,8 @@ __global__ __launch_bounds__(64 * kF32Waves, kF32Waves * kF32PerCu / 4) void gro
   const int lrow = lane & 15, quarter = lane >> 4;
   const int K = MODE == MODE_GATEUP ? p.H : p.F;
   const int ES = p.E + p.S;
-  ItemQueue q(p, (long long)(*p.n_tiles) * n_ntiles);
-  if (tid == 0) *s_next = q.settle(q.draw());
+  ItemQueue q(p, n_ntiles);
+  if (tid == 0) *s_next = q.first();
   __syncthreads();
   int it = __builtin_amdgcn_readfirstlane(*s_next);
 
@@ -1120,6 +1146,19 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
 }  // namespace
 
 int gemm_bm(int dtype) { return dtype == EB_DTYPE_BF16 ? BM : FBM; }
+
+// Row blocks to set aside for the end of a launch (see ItemQueue): about one
+// and a half items per workgroup, from groups of up to half a tile, whose
+// items take half as long as a full tile's.  Without them the workgroups
+// ended up to one long item apart: 44700 rows in 128 groups at H = 2048,
+// F = 1408 700 -> 597 us (gate/up) and 380 -> 327 us (down) on one box, steps
+// of 128-token micro-batches 218 -> 211 and 126 -> 116 us; a third fewer or
+// more measure the same.  fp32 items are short as they are (no gain).
+TailRule gemm_tail(int dtype, int F) {
+  if (dtype != EB_DTYPE_BF16) return TailRule{0, 0};
+  const int nsub = F / (BN / 2);
+  return TailRule{(384 + nsub - 1) / nsub, BM / 2};
+}
 
 hipError_t launch_pack_weights(int dtype, int gateup, int n, int N, int K, int F, const void* src,
                                void* dst, hipStream_t s) {

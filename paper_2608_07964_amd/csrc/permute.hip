@@ -88,15 +88,15 @@ __device__ int block_exclusive_scan(int v, int* wtot, int* total) {
 template <class RTA>
 __global__ __launch_bounds__(kScanThreads) void perm_scan_kernel(
     RTA rta, const int32_t* __restrict__ hist, int32_t* __restrict__ chunk_base,
-    int32_t* __restrict__ offsets, int4* __restrict__ tiles, int bm, int max_tiles,
-    int32_t* __restrict__ work_ctr) {
+    int32_t* __restrict__ offsets, int4* __restrict__ tiles, int bm, TailRule tail,
+    int max_tiles, int32_t* __restrict__ work_ctr) {
   __shared__ int running[kMaxKeys];              // per-key totals, then offsets / cursors
   __shared__ int hl[kHistWindow];                // one window of histogram cells
   __shared__ int wtot[kScanWaves];
   __shared__ int s_cb[EB_MAX_RUN + 1], s_tb[EB_MAX_RUN + 1], s_ly[EB_MAX_RUN];
   const RunTable& rt = rta.get();
   const int tid = threadIdx.x;
-  if (tid < kWorkWords && tid != kWorkTiles) work_ctr[tid] = 0;
+  if (tid < kWorkWords && tid != kWorkTiles && tid != kWorkTiles + 1) work_ctr[tid] = 0;
   const int E = rt.E, ES = rt.E + rt.S, n = rt.n;
   const int n_chunks = rt.chunk_base[n];
   const int n_keys = rt.L * ES;
@@ -148,22 +148,36 @@ __global__ __launch_bounds__(kScanThreads) void perm_scan_kernel(
   if (tid == 0) offsets[n_keys] = total;
   __syncthreads();
 
-  // 3) tile list: ceil(M/bm) row blocks per non-empty key, keys ascending
+  // 3) tile list: ceil(M/bm) row blocks per non-empty key, keys ascending,
+  //    the first tail.tiles groups of at most tail.rows rows (one block each,
+  //    tail.rows <= bm) after all the others
   auto rows_of = [&](int i) { return (i + 1 < n_keys ? running[i + 1] : total) - running[i]; };
-  int local_tiles = 0;
-  for (int i = k0; i < k1; ++i) local_tiles += (rows_of(i) + bm - 1) / bm;
-  int tiles_total = 0;
+  int local_tiles = 0, local_small = 0;
+  for (int i = k0; i < k1; ++i) {
+    const int M = rows_of(i);
+    local_tiles += (M + bm - 1) / bm;
+    local_small += M > 0 && M <= tail.rows;
+  }
+  int tiles_total = 0, small_total = 0;
   int tb = block_exclusive_scan(local_tiles, wtot, &tiles_total);
+  int sb = block_exclusive_scan(local_small, wtot, &small_total);
+  const int main_total = tiles_total - min(small_total, tail.tiles);
   for (int i = k0; i < k1; ++i) {
     const int r0 = running[i], M = rows_of(i);
     if (M == 0) continue;
-    const int4 g = make_int4(i, r0, M, tb);
-    for (int m = 0; m < M; m += bm) {
-      if (tb < max_tiles) tiles[tb] = g;
-      ++tb;
-    }
+    const bool small = M <= tail.rows;
+    const int at = small && sb < tail.tiles ? main_total + sb : tb - min(sb, tail.tiles);
+    const int4 g = make_int4(i, r0, M, at);
+    const int n = (M + bm - 1) / bm;
+    for (int m = 0; m < n; ++m)
+      if (at + m < max_tiles) tiles[at + m] = g;
+    tb += n;
+    sb += small;
   }
-  if (tid == 0) work_ctr[kWorkTiles] = min(tiles_total, max_tiles);
+  if (tid == 0) {
+    work_ctr[kWorkTiles] = min(tiles_total, max_tiles);
+    work_ctr[kWorkTiles + 1] = min(main_total, max_tiles);
+  }
   __syncthreads();  // running[] becomes the cursors below
 
   // 4) per-chunk bases: for every column, the entries' chunks in order; a
@@ -296,10 +310,10 @@ void perm_count_impl(RTA a, int grid, int32_t* hist, hipStream_t s) {
 
 template <class RTA>
 void perm_scan_impl(RTA a, const int32_t* hist, int32_t* chunk_base, int32_t* offsets, int4* tiles,
-                    int bm, int max_tiles, int32_t* work_ctr, hipStream_t s) {
+                    int bm, TailRule tail, int max_tiles, int32_t* work_ctr, hipStream_t s) {
   prof_start(EB_K_PERM_SCAN, s);
   hipLaunchKernelGGL(perm_scan_kernel<RTA>, dim3(1), dim3(kScanThreads), 0, s, a, hist, chunk_base,
-                     offsets, tiles, bm, max_tiles, work_ctr);
+                     offsets, tiles, bm, tail, max_tiles, work_ctr);
   prof_stop(EB_K_PERM_SCAN, s);
 }
 
@@ -337,10 +351,10 @@ hipError_t launch_perm_count(const RunTable& rt, int n_chunks, int32_t* hist, hi
 }
 
 hipError_t launch_perm_scan(const RunTable& rt, const int32_t* hist, int32_t* chunk_base,
-                            int32_t* offsets, int4* tiles, int bm, int max_tiles, int32_t* work_ctr,
-                            hipStream_t s) {
+                            int32_t* offsets, int4* tiles, int bm, TailRule tail, int max_tiles,
+                            int32_t* work_ctr, hipStream_t s) {
   if (!scan_fits(rt.L, rt.E, rt.S, rt.n)) return hipErrorInvalidValue;
-  perm_scan_impl(ByValue<RunTable>{rt}, hist, chunk_base, offsets, tiles, bm, max_tiles, work_ctr, s);
+  perm_scan_impl(ByValue<RunTable>{rt}, hist, chunk_base, offsets, tiles, bm, tail, max_tiles, work_ctr, s);
   return hipGetLastError();
 }
 
@@ -358,7 +372,8 @@ hipError_t launch_permute_dev(const eb_model_desc& d, const RunTable* rt, int ma
   const InMemory<RunTable> a{rt};
   const int eb = d.dtype == EB_DTYPE_BF16 ? 2 : 4;
   perm_count_impl(a, max_chunks, b.hist, s);
-  perm_scan_impl(a, b.hist, b.chunk_base, b.offsets, b.tiles, gemm_bm(d.dtype), b.max_tiles, b.work_ctr, s);
+  perm_scan_impl(a, b.hist, b.chunk_base, b.offsets, b.tiles, gemm_bm(d.dtype),
+                 gemm_tail(d.dtype, d.F), b.max_tiles, b.work_ctr, s);
   perm_scatter_impl(a, d.H, max_chunks, max_tokens, eb, b.chunk_base, b.perm, b.inv,
                     b.a_perm, s);
   return hipGetLastError();
