@@ -69,7 +69,7 @@ StepShape step_shape(const eb_model_desc& d, int n_run, const int32_t* T) {
 }
 
 struct WsLayout {
-  size_t hist, chunk_base, offsets, tiles, work_ctr, partial, perm, a_perm, h, total;
+  size_t hist, chunk_base, offsets, tiles, work_ctr, partial, a_perm, h, total;
 };
 
 WsLayout ws_layout(const eb_model_desc& d, const StepShape& s, const eb_step_views* v) {
@@ -87,7 +87,7 @@ WsLayout ws_layout(const eb_model_desc& d, const StepShape& s, const eb_step_vie
   w.tiles = take(sizeof(int4) * (size_t)(s.max_tiles > 0 ? s.max_tiles : 1));
   w.work_ctr = take(sizeof(int32_t) * kWorkWords);
   w.partial = down_ksplit(d.dtype, d.F) > 1 ? take(sizeof(float) * 2 * (size_t)s.P * d.H) : 0;
-  w.perm = (v && v->perm) ? 0 : take(sizeof(int32_t) * (size_t)s.P);
+  if (!(v && v->perm)) take(sizeof(int32_t) * (size_t)s.P);  // not written; part of the published size
   w.a_perm = (v && v->a_perm) ? 0 : take(eb * (size_t)s.P * d.H);
   w.h = (v && v->h) ? 0 : take(eb * (size_t)s.P * d.F);
   w.total = off;
@@ -163,7 +163,7 @@ StepWs carve_step(const eb_model_desc& d, const StepShape& sh, const eb_step_vie
   b.tiles = reinterpret_cast<int4*>(base + L.tiles);
   b.work_ctr = reinterpret_cast<int32_t*>(base + L.work_ctr);
   b.max_tiles = sh.max_tiles;
-  b.perm = (views && views->perm) ? views->perm : reinterpret_cast<int32_t*>(base + L.perm);
+  b.perm = views ? views->perm : nullptr;
   b.inv = inv;
   b.a_perm = (views && views->a_perm) ? views->a_perm : base + L.a_perm;
   w.partial = L.partial ? reinterpret_cast<float*>(base + L.partial) : nullptr;
@@ -233,7 +233,7 @@ int enqueue_step_dev(const eb_model_desc& d, int N, int T, const RunTable* rt, c
   const StepShape sh = step_shape(d, N, Ts.data());
   const StepWs w = carve_step(d, sh, nullptr, ws, inv);
   int rc;
-  if ((rc = hip_status(launch_permute_dev(d, rt, sh.n_chunks, (int)sh.tokens, w.b, s), "permute")))
+  if ((rc = hip_status(launch_permute_dev(d, rt, N, T, w.b, s), "permute")))
     return rc;
   // a split-K down GEMM leaves its two fp32 halves for the combine, which
   // rounds their sum as the split-K sum kernel would (o is not stored)
@@ -385,16 +385,7 @@ int moe_step_common(const eb_model_desc* desc, int32_t n_run, const eb_work* run
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   const RunTable rt = make_run_table(d, n_run, run, nullptr);
-  const int eb = d.dtype == EB_DTYPE_BF16 ? 2 : 4;
-  const StepBuffers& b = w.b;
-  if ((rc = hip_status(launch_perm_count(rt, sh.n_chunks, b.hist, s), "perm_count"))) return rc;
-  if ((rc = hip_status(launch_perm_scan(rt, b.hist, b.chunk_base, b.offsets, b.tiles, gemm_bm(d.dtype),
-                                        gemm_tail(d.dtype, d.F), b.max_tiles, b.work_ctr, s),
-                       "perm_scan")))
-    return rc;
-  if ((rc = hip_status(launch_perm_scatter(rt, sh.n_chunks, eb, b.chunk_base, b.perm, inv_out, b.a_perm, s),
-                       "perm_scatter")))
-    return rc;
+  if ((rc = hip_status(launch_permute(d, rt, w.b, s), "permute"))) return rc;
   return run_gemms(d, sh, w, wt, o_out, s);
 }
 

@@ -190,14 +190,6 @@ hipError_t launch_route(const eb_model_desc& d, int T, const float* x, const flo
                         const void* Wg, const float* bias, void* a_out, float* logits,
                         int32_t* idx, float* w, int32_t* counts, hipStream_t s);
 
-hipError_t launch_perm_count(const RunTable& rt, int n_chunks, int32_t* hist, hipStream_t s);
-hipError_t launch_perm_scan(const RunTable& rt, const int32_t* hist, int32_t* chunk_base,
-                            int32_t* offsets, int4* tiles, int bm, TailRule tail, int max_tiles,
-                            int32_t* work_ctr, hipStream_t s);
-hipError_t launch_perm_scatter(const RunTable& rt, int n_chunks, int elem_bytes,
-                               const int32_t* chunk_base, int32_t* perm, int32_t* inv,
-                               void* a_perm, hipStream_t s);
-
 // Workspace buffers of one step (see the workspace layout in api.cpp).
 struct StepBuffers {
   int32_t* hist;
@@ -206,16 +198,18 @@ struct StepBuffers {
   int4* tiles;
   int32_t* work_ctr;       // [kWorkWords]
   int32_t max_tiles;
-  int32_t* perm;
+  int32_t* perm;           // or null: nothing in a step reads it, it is for callers that ask
   int32_t* inv;
   void* a_perm;
 };
 
-// Count, scan, scatter and gather of a step whose run table a device-side
-// scheduler wrote to `rt` (device memory); grids cover max_chunks chunks and
-// max_tokens tokens, the largest step's.
-hipError_t launch_permute_dev(const eb_model_desc& d, const RunTable* rt, int max_chunks,
-                              int max_tokens, const StepBuffers& b, hipStream_t s);
+// Grouping of a step: perm, inv, offsets, tile list, a_perm; work counters
+// cleared.
+hipError_t launch_permute(const eb_model_desc& d, const RunTable& rt, const StepBuffers& b, hipStream_t s);
+// The same for a run table that a device-side scheduler wrote to `rt` (device
+// memory); grids cover N entries of T tokens, the largest step.
+hipError_t launch_permute_dev(const eb_model_desc& d, const RunTable* rt, int N, int T, const StepBuffers& b,
+                              hipStream_t s);
 
 // Row-block height of the grouped GEMM tiles for a dtype.
 int gemm_bm(int dtype);

@@ -10,9 +10,11 @@
 //                        key, first row, rows, index of its first row block);
 //                        it also clears the work counters of the step's
 //                        grouped GEMM launches
+//                        (the three above and perm_scatter_kernel: one launch,
+//                        perm_small_kernel, for steps of up to about 1000 tokens)
 //   perm_scatter_kernel  per chunk: stable rank of each pair inside its key from
 //                        per-wavefront 64-bit expert masks (popcount of the lanes
-//                        below), then inv and perm
+//                        below), then inv, and perm where a caller asks for it
 //   gather_tokens_kernel one wavefront per (token, 1 KB piece of its row):
 //                        the piece, read once, to a_perm[inv[q]] for each of
 //                        the token's k+S pairs q
@@ -81,6 +83,61 @@ __device__ int block_exclusive_scan(int v, int* wtot, int* total) {
   return before + x - v;
 }
 
+// Offsets and GEMM tile list from the per-key totals in running[] (1024
+// threads, running[] complete); leaves each key's offset in running[].
+__device__ void offsets_and_tiles(int* running, int n_keys, int* wtot, int32_t* __restrict__ offsets,
+                                  int4* __restrict__ tiles, int bm, TailRule tail, int max_tiles,
+                                  int32_t* __restrict__ work_ctr) {
+  const int tid = threadIdx.x;
+  // exclusive scan over keys -> offsets; thread tid owns a contiguous span
+  const int span = (n_keys + kScanThreads - 1) / kScanThreads;
+  const int k0 = min(tid * span, n_keys), k1 = min(k0 + span, n_keys);
+  int local = 0;
+  for (int i = k0; i < k1; ++i) local += running[i];
+  int total = 0;
+  int base = block_exclusive_scan(local, wtot, &total);
+  for (int i = k0; i < k1; ++i) {
+    const int v = running[i];
+    offsets[i] = base;
+    running[i] = base;  // becomes the running cursor of key i
+    base += v;
+  }
+  if (tid == 0) offsets[n_keys] = total;
+  __syncthreads();
+
+  // tile list: ceil(M/bm) row blocks per non-empty key, keys ascending,
+  //    the first tail.tiles groups of at most tail.rows rows (one block each,
+  //    tail.rows <= bm) after all the others
+  auto rows_of = [&](int i) { return (i + 1 < n_keys ? running[i + 1] : total) - running[i]; };
+  int local_tiles = 0, local_small = 0;
+  for (int i = k0; i < k1; ++i) {
+    const int M = rows_of(i);
+    local_tiles += (M + bm - 1) / bm;
+    local_small += M > 0 && M <= tail.rows;
+  }
+  int tiles_total = 0, small_total = 0;
+  int tb = block_exclusive_scan(local_tiles, wtot, &tiles_total);
+  int sb = block_exclusive_scan(local_small, wtot, &small_total);
+  const int main_total = tiles_total - min(small_total, tail.tiles);
+  for (int i = k0; i < k1; ++i) {
+    const int r0 = running[i], M = rows_of(i);
+    if (M == 0) continue;
+    const bool small = M <= tail.rows;
+    const int at = small && sb < tail.tiles ? main_total + sb : tb - min(sb, tail.tiles);
+    const int4 g = make_int4(i, r0, M, at);
+    const int n = (M + bm - 1) / bm;
+    for (int m = 0; m < n; ++m)
+      if (at + m < max_tiles) tiles[at + m] = g;
+    tb += n;
+    sb += small;
+  }
+  if (tid == 0) {
+    work_ctr[kWorkTiles] = min(tiles_total, max_tiles);
+    work_ctr[kWorkTiles + 1] = min(main_total, max_tiles);
+  }
+  __syncthreads();  // running[] may change from here on
+}
+
 // offsets: [L*(E+S)+1]; chunk_base: [n_chunks][E+S]; tiles: [max_tiles].
 // The histogram cells (chunk b, column c) go through LDS in windows of
 // kHistWindow / (E+S) chunks (one window unless the step is very large);
@@ -132,53 +189,8 @@ __global__ __launch_bounds__(kScanThreads) void perm_scan_kernel(
   }
   __syncthreads();
 
-  // 2) exclusive scan over keys -> offsets; thread tid owns a contiguous span
-  const int span = (n_keys + kScanThreads - 1) / kScanThreads;
-  const int k0 = min(tid * span, n_keys), k1 = min(k0 + span, n_keys);
-  int local = 0;
-  for (int i = k0; i < k1; ++i) local += running[i];
-  int total = 0;
-  int base = block_exclusive_scan(local, wtot, &total);
-  for (int i = k0; i < k1; ++i) {
-    const int v = running[i];
-    offsets[i] = base;
-    running[i] = base;  // becomes the running cursor of key i
-    base += v;
-  }
-  if (tid == 0) offsets[n_keys] = total;
-  __syncthreads();
-
-  // 3) tile list: ceil(M/bm) row blocks per non-empty key, keys ascending,
-  //    the first tail.tiles groups of at most tail.rows rows (one block each,
-  //    tail.rows <= bm) after all the others
-  auto rows_of = [&](int i) { return (i + 1 < n_keys ? running[i + 1] : total) - running[i]; };
-  int local_tiles = 0, local_small = 0;
-  for (int i = k0; i < k1; ++i) {
-    const int M = rows_of(i);
-    local_tiles += (M + bm - 1) / bm;
-    local_small += M > 0 && M <= tail.rows;
-  }
-  int tiles_total = 0, small_total = 0;
-  int tb = block_exclusive_scan(local_tiles, wtot, &tiles_total);
-  int sb = block_exclusive_scan(local_small, wtot, &small_total);
-  const int main_total = tiles_total - min(small_total, tail.tiles);
-  for (int i = k0; i < k1; ++i) {
-    const int r0 = running[i], M = rows_of(i);
-    if (M == 0) continue;
-    const bool small = M <= tail.rows;
-    const int at = small && sb < tail.tiles ? main_total + sb : tb - min(sb, tail.tiles);
-    const int4 g = make_int4(i, r0, M, at);
-    const int n = (M + bm - 1) / bm;
-    for (int m = 0; m < n; ++m)
-      if (at + m < max_tiles) tiles[at + m] = g;
-    tb += n;
-    sb += small;
-  }
-  if (tid == 0) {
-    work_ctr[kWorkTiles] = min(tiles_total, max_tiles);
-    work_ctr[kWorkTiles + 1] = min(main_total, max_tiles);
-  }
-  __syncthreads();  // running[] becomes the cursors below
+  // 2), 3)
+  offsets_and_tiles(running, n_keys, wtot, offsets, tiles, bm, tail, max_tiles, work_ctr);
 
   // 4) per-chunk bases: for every column, the entries' chunks in order; a
   //    key's cursor lives in LDS across entries, in a register within one
@@ -246,8 +258,129 @@ __global__ __launch_bounds__(kPermChunk) void perm_scatter_kernel(
         pos = cb[E + (r - k)] + threadIdx.x;  // every token of the chunk has it
       }
       inv[q0 + r] = pos;
-      perm[pos] = (int32_t)(q0 + r);
+      if (perm) perm[pos] = (int32_t)(q0 + r);
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Count, scan and scatter of a small step in one workgroup.  The three
+// launches above each take about 5 us for a step of a few hundred tokens
+// whatever they do, one after the other; here the pairs of 64 tokens at a time
+// (a piece, one token per lane) are counted in LDS, scanned and placed without
+// leaving the CU.  The same integers as the three kernels give.
+// It costs about 7 us plus 65 ns per slot of a piece (LDS atomics, then
+// scattered stores, all from one CU): 16 pieces of 8 slots over 64 experts 15
+// us against 17 (5 + 7 + 5) for the three launches, 32 pieces of 8 slots 24 us
+// against 20, 32 of 2 slots 16 us; hence the limits.
+constexpr int kSmallPieces = 32;      // pieces of a small step
+constexpr int kSmallSlots = 128;      // pieces x slots of a small step
+constexpr int kSmallWords = 23040;    // LDS words for the pieces' expert masks and counts (90 KB)
+static_assert(EB_MAX_RUN <= kWave, "one lane per entry");
+
+template <class RTA>
+__global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
+    RTA rta, int32_t* __restrict__ offsets, int4* __restrict__ tiles, int bm, TailRule tail, int max_tiles,
+    int32_t* __restrict__ work_ctr, int32_t* __restrict__ perm, int32_t* __restrict__ inv) {
+  __shared__ int running[kMaxKeys];                        // per-key totals, then offsets / cursors
+  __shared__ unsigned long long masks[kSmallWords / 2];    // [pieces][E] lanes per expert, then the counts
+  __shared__ int wtot[kScanWaves], s_layer[kSmallPieces];
+  const RunTable& rt = rta.get();
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int E = rt.E, S = rt.S, k = rt.k, n = rt.n, ES = E + S, slots = k + S, n_keys = rt.L * ES;
+
+  // lane i: entry i's first piece (pieces of an entry in token order, entries in order)
+  const int tok0 = lane < n ? rt.tok_base[lane] : 0, len = lane < n ? rt.tok_base[lane + 1] - tok0 : 0;
+  int upto = (len + kWave - 1) / kWave;
+  const int own = upto;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int y = __shfl_up(upto, off, kWave);
+    if (lane >= off) upto += y;
+  }
+  const int np = min(__shfl(upto, kWave - 1, kWave), kSmallPieces);
+  int* cnt = reinterpret_cast<int*>(masks + np * E);       // [pieces][ES] counts, then first positions
+
+  // this lane's token of piece p and its picks
+  struct Token {
+    int rho, q0, rows;     // entry, first pair, tokens of the piece
+    int e[kMaxSlots];
+  } tk;
+  auto load = [&](int p) {
+    tk.rho = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < n && upto <= p)));
+    const int t0 = (p - __shfl(upto - own, tk.rho, kWave)) * kWave;
+    tk.rows = min(kWave, __shfl(len, tk.rho, kWave) - t0);
+    tk.q0 = (__shfl(tok0, tk.rho, kWave) + t0 + lane) * slots;
+    const int32_t* ix = in_global(rt.idx[tk.rho]) + (size_t)(t0 + lane) * k;
+#pragma unroll
+    for (int r = 0; r < kMaxSlots; ++r)
+      if (r < k && lane < tk.rows) tk.e[r] = clamp_expert(ix[r], E);
+  };
+  int p_last = -1;         // the piece in tk
+  if (wave < np) load(p_last = wave);
+
+  if (tid < kWorkWords && tid != kWorkTiles && tid != kWorkTiles + 1) work_ctr[tid] = 0;
+  for (int i = tid; i < n_keys; i += kScanThreads) running[i] = 0;
+  for (int i = tid; i < np * E; i += kScanThreads) masks[i] = 0ull;
+  for (int i = tid; i < np * ES; i += kScanThreads) cnt[i] = 0;
+  __syncthreads();
+  for (int p = wave; p < np; p += kScanWaves) {
+    if (p != p_last) load(p_last = p);
+    if (lane == 0) s_layer[p] = rt.layer[tk.rho];
+    if (lane < S) cnt[p * ES + E + lane] = tk.rows;
+#pragma unroll
+    for (int r = 0; r < kMaxSlots; ++r)
+      if (r < k && lane < tk.rows) {
+        atomicOr(&masks[p * E + tk.e[r]], 1ull << lane);
+        atomicAdd(&cnt[p * ES + tk.e[r]], 1);
+      }
+  }
+  __syncthreads();
+  for (int i = tid; i < np * ES; i += kScanThreads) {
+    const int p = i / ES;
+    const int v = cnt[i];
+    if (v) atomicAdd(&running[s_layer[p] * ES + i - p * ES], v);
+  }
+  __syncthreads();
+  offsets_and_tiles(running, n_keys, wtot, offsets, tiles, bm, tail, max_tiles, work_ctr);
+  // first position of every (piece, column): the pieces in order
+  for (int c = tid; c < ES; c += kScanThreads) {
+    int layer = -1, cur = 0;
+    for (int p0 = 0; p0 < np; p0 += 8) {
+      int v[8], l[8];  // read ahead of the stores
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (p0 + j < np) {
+          v[j] = cnt[(p0 + j) * ES + c];
+          l[j] = s_layer[p0 + j];
+        }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (p0 + j < np) {
+          if (l[j] != layer) {
+            if (layer >= 0) running[layer * ES + c] = cur;
+            cur = running[l[j] * ES + c];
+            layer = l[j];
+          }
+          cnt[(p0 + j) * ES + c] = cur;
+          cur += v[j];
+        }
+    }
+  }
+  __syncthreads();
+  for (int p = p_last; p >= 0; p -= kScanWaves) {
+    if (p != p_last) load(p);
+    if (lane >= tk.rows) continue;
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int r = 0; r < kMaxSlots; ++r)
+      if (r < slots) {
+        const int pos = r < k ? cnt[p * ES + tk.e[r]] + __popcll(masks[p * E + tk.e[r]] & below)
+                              : cnt[p * ES + E + (r - k)] + lane;
+        inv[tk.q0 + r] = pos;
+        if (perm) perm[pos] = tk.q0 + r;
+      }
   }
 }
 
@@ -317,16 +450,32 @@ void perm_scan_impl(RTA a, const int32_t* hist, int32_t* chunk_base, int32_t* of
   prof_stop(EB_K_PERM_SCAN, s);
 }
 
-// grid_chunks / grid_tokens: chunks and tokens the grids cover
 template <class RTA>
-void perm_scatter_impl(RTA a, int H, int grid_chunks, int grid_tokens, int elem_bytes,
-                       const int32_t* chunk_base, int32_t* perm, int32_t* inv, void* a_perm,
-                       hipStream_t s) {
+void perm_scatter_impl(RTA a, int grid_chunks, const int32_t* chunk_base, int32_t* perm, int32_t* inv, hipStream_t s) {
   prof_start(EB_K_PERM_SCATTER, s);
   if (grid_chunks > 0)
     hipLaunchKernelGGL(perm_scatter_kernel<RTA>, dim3(grid_chunks), dim3(kPermChunk), 0, s, a,
                        chunk_base, perm, inv);
   prof_stop(EB_K_PERM_SCATTER, s);
+}
+
+// Whether a step of `pieces` 64-token pieces runs in perm_small_kernel: the
+// pieces' masks and counts fit its LDS, and there are few enough of them that
+// one workgroup is faster than three launches (measured there).
+bool perm_small(const eb_model_desc& d, int pieces) {
+  return pieces <= kSmallPieces && pieces * (d.k + d.S) <= kSmallSlots && pieces * (3 * d.E + d.S) <= kSmallWords;
+}
+
+template <class RTA>
+void perm_small_impl(RTA a, const StepBuffers& b, int bm, TailRule tail, hipStream_t s) {
+  prof_start(EB_K_PERM_SCAN, s);
+  hipLaunchKernelGGL(perm_small_kernel<RTA>, dim3(1), dim3(kScanThreads), 0, s, a, b.offsets, b.tiles, bm, tail,
+                     b.max_tiles, b.work_ctr, b.perm, b.inv);
+  prof_stop(EB_K_PERM_SCAN, s);
+}
+
+template <class RTA>
+void gather_impl(RTA a, int H, int grid_tokens, int elem_bytes, const int32_t* inv, void* a_perm, hipStream_t s) {
   const size_t row_bytes = (size_t)H * elem_bytes;
   prof_start(EB_K_PERM_GATHER, s);
   if (grid_tokens > 0) {
@@ -339,43 +488,42 @@ void perm_scatter_impl(RTA a, int H, int grid_chunks, int grid_tokens, int elem_
   prof_stop(EB_K_PERM_GATHER, s);
 }
 
+// The whole grouping: grid_chunks / grid_tokens are the chunks and tokens the
+// grids cover, pieces the most 64-token pieces the entries can have.
+template <class RTA>
+void permute_impl(RTA a, const eb_model_desc& d, int grid_chunks, int grid_tokens, int pieces, const StepBuffers& b,
+                  hipStream_t s) {
+  const int bm = gemm_bm(d.dtype);
+  const TailRule tail = gemm_tail(d.dtype, d.F);
+  if (perm_small(d, pieces)) {
+    perm_small_impl(a, b, bm, tail, s);
+  } else {
+    perm_count_impl(a, grid_chunks, b.hist, s);
+    perm_scan_impl(a, b.hist, b.chunk_base, b.offsets, b.tiles, bm, tail, b.max_tiles, b.work_ctr, s);
+    perm_scatter_impl(a, grid_chunks, b.chunk_base, b.perm, b.inv, s);
+  }
+  gather_impl(a, d.H, grid_tokens, d.dtype == EB_DTYPE_BF16 ? 2 : 4, b.inv, b.a_perm, s);
+}
+
 bool scan_fits(int L, int E, int S, int n) {
   return (long)L * (E + S) <= kMaxKeys && E + S <= kScanThreads && n <= EB_MAX_RUN;
 }
 
 }  // namespace
 
-hipError_t launch_perm_count(const RunTable& rt, int n_chunks, int32_t* hist, hipStream_t s) {
-  perm_count_impl(ByValue<RunTable>{rt}, n_chunks, hist, s);
+hipError_t launch_permute(const eb_model_desc& d, const RunTable& rt, const StepBuffers& b, hipStream_t s) {
+  if (!scan_fits(d.L, d.E, d.S, rt.n)) return hipErrorInvalidValue;
+  int pieces = 0;
+  for (int i = 0; i < rt.n; ++i) pieces += (rt.tok_base[i + 1] - rt.tok_base[i] + kWave - 1) / kWave;
+  permute_impl(ByValue<RunTable>{rt}, d, rt.chunk_base[rt.n], rt.tok_base[rt.n], pieces, b, s);
   return hipGetLastError();
 }
 
-hipError_t launch_perm_scan(const RunTable& rt, const int32_t* hist, int32_t* chunk_base,
-                            int32_t* offsets, int4* tiles, int bm, TailRule tail, int max_tiles,
-                            int32_t* work_ctr, hipStream_t s) {
-  if (!scan_fits(rt.L, rt.E, rt.S, rt.n)) return hipErrorInvalidValue;
-  perm_scan_impl(ByValue<RunTable>{rt}, hist, chunk_base, offsets, tiles, bm, tail, max_tiles, work_ctr, s);
-  return hipGetLastError();
-}
-
-hipError_t launch_perm_scatter(const RunTable& rt, int n_chunks, int elem_bytes,
-                               const int32_t* chunk_base, int32_t* perm, int32_t* inv,
-                               void* a_perm, hipStream_t s) {
-  perm_scatter_impl(ByValue<RunTable>{rt}, rt.H, n_chunks, rt.tok_base[rt.n], elem_bytes,
-                    chunk_base, perm, inv, a_perm, s);
-  return hipGetLastError();
-}
-
-hipError_t launch_permute_dev(const eb_model_desc& d, const RunTable* rt, int max_chunks,
-                              int max_tokens, const StepBuffers& b, hipStream_t s) {
+hipError_t launch_permute_dev(const eb_model_desc& d, const RunTable* rt, int N, int T, const StepBuffers& b,
+                              hipStream_t s) {
   if (!scan_fits(d.L, d.E, d.S, 0)) return hipErrorInvalidValue;
-  const InMemory<RunTable> a{rt};
-  const int eb = d.dtype == EB_DTYPE_BF16 ? 2 : 4;
-  perm_count_impl(a, max_chunks, b.hist, s);
-  perm_scan_impl(a, b.hist, b.chunk_base, b.offsets, b.tiles, gemm_bm(d.dtype),
-                 gemm_tail(d.dtype, d.F), b.max_tiles, b.work_ctr, s);
-  perm_scatter_impl(a, d.H, max_chunks, max_tokens, eb, b.chunk_base, b.perm, b.inv,
-                    b.a_perm, s);
+  permute_impl(InMemory<RunTable>{rt}, d, N * ((T + kPermChunk - 1) / kPermChunk), N * T,
+               N * ((T + kWave - 1) / kWave), b, s);
   return hipGetLastError();
 }
 

@@ -1,0 +1,70 @@
+"""A step's grouping (perm, inv, offsets, gathered rows) against the oracle's
+stable permutation, on both sides of the one-workgroup kernel's limits: 32
+pieces of up to 64 tokens, 128 pieces x slots, 23040 LDS words.  All integers and copies: exact."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import log
+from oracle import permute as operm
+
+pytestmark = pytest.mark.gpu
+
+
+# name: (dtype, L, E, S, k, tokens of each entry); layers cycle, so one layer's
+# entries are not neighbours
+CASES = {
+    "one_token": ("bf16", 1, 64, 2, 6, [1]),
+    "piece_edges": ("bf16", 2, 60, 4, 4, [63, 64, 65, 0, 127, 128, 129, 1]),
+    "many_entries": ("bf16", 5, 8, 0, 2, [1 + i % 7 for i in range(32)]),
+    "64_entries": ("bf16", 5, 8, 0, 2, [1 + i % 7 for i in range(64)]),
+    "32_pieces": ("bf16", 2, 16, 1, 3, [1024, 1, 64, 895]),
+    "33_pieces": ("bf16", 2, 16, 1, 3, [1024, 1, 65, 895]),
+    "slots_full": ("bf16", 3, 256, 0, 8, [65] * 8),
+    "slots_over": ("bf16", 3, 256, 1, 8, [65] * 8),
+    "lds_full": ("bf16", 3, 256, 0, 1, [64] * 30),
+    "lds_over": ("bf16", 3, 256, 0, 1, [64] * 31),
+    "many_keys": ("f32", 15, 1000, 4, 12, [64, 3, 64, 130]),
+    "all_slots": ("f32", 3, 20, 0, 16, [70, 0, 90]),
+    "three_launches": ("f32", 3, 500, 2, 5, [300, 1, 512, 77, 256]),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_grouping(name, device):
+    from paper_2608_07964_amd import binding as B
+    log(f"grouping {name}")
+    dtype, L, E, S, k, lens = CASES[name]
+    H, F = 256, 128
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = np.random.default_rng(11)
+    g = torch.Generator(device=device).manual_seed(11)
+    layers = [i % L for i in range(len(lens))]
+    # skewed picks: the low experts take most tokens
+    idx = [np.argsort(rng.random((T, E)) * (1.0 + np.arange(E)) ** 0.7, axis=1)[:, :k] for T in lens]
+    a = [torch.randn(max(T, 1), H, generator=g, device=device).to(tdt) for T in lens]
+    used = sorted(set(layers))
+    gu = [torch.zeros(E + S, 2 * F, H, dtype=tdt, device=device) if l in used else None for l in range(L)]
+    dn = [torch.zeros(E + S, H, F, dtype=tdt, device=device) if l in used else None for l in range(L)]
+    desc = B.make_desc(L, H, F, E, k, S, 1, dtype)
+    P = sum(lens) * (k + S)
+    keep = [torch.from_numpy(np.ascontiguousarray(i, np.int32)).to(device) for i in idx]
+    w = torch.ones(max(lens), k, device=device)
+    run = B.work_array([(j, l, T, x, i, w) for j, (l, T, x, i) in enumerate(zip(layers, lens, a, keep))])
+    o = torch.full((P, H), 1.0, dtype=tdt, device=device)
+    inv = torch.full((P,), -1, dtype=torch.int32, device=device)
+    v = dict(a_perm=torch.zeros(P, H, dtype=tdt, device=device), h=torch.empty(P, F, dtype=tdt, device=device),
+             perm=torch.full((P,), -1, dtype=torch.int32, device=device),
+             offsets=torch.full((L * (E + S) + 1,), -1, dtype=torch.int32, device=device))
+    wsb = B.easybalance_moe_step_workspace_size(desc, lens)
+    ws = torch.full((wsb + 256,), 255, dtype=torch.uint8, device=device)
+    B.easybalance_moe_step(desc, run, len(lens), gu, dn, ws.data_ptr() + (-ws.data_ptr()) % 256, wsb, o, inv, v)
+    torch.cuda.synchronize()
+    perm, want_inv, offsets = operm.stable_permutation(operm.step_keys(list(zip(layers, idx)), E, S), L * (E + S))
+    assert np.array_equal(v["offsets"].cpu().numpy(), offsets)
+    assert np.array_equal(v["perm"].cpu().numpy(), perm)
+    assert np.array_equal(inv.cpu().numpy(), want_inv)
+    src = torch.cat([x[:T] for x, T in zip(a, lens)])
+    rows = torch.from_numpy(perm // (k + S)).to(device)
+    assert torch.equal(v["a_perm"], src[rows])
+    assert not o.any()                               # zero experts: every row was computed
