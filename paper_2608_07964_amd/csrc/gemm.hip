@@ -63,8 +63,21 @@ constexpr int kBPart = kBLoads / (BK / 16);      // B loads issued per k-step
 static_assert(kBPart * (BK / 16) == kBLoads, "B loads split evenly over the k-steps");
 constexpr int kXcds = 8;
 
-template <int BM_, int WM_, int SA_, int SB_>
+// Weights that one workgroup alone reads are loaded with the nt cache policy
+// where a launch does little but stream them: they then leave the L2 and the
+// memory-side cache alone, and HBM delivers 6.2 instead of 5.5 TB/s (64 tokens
+// on 8 experts of H = 4096, F = 14336: step 495 -> 454 us).
+constexpr int kNonTemporal = 2;  // bit nt of a buffer load's cache policy
+// Most tokens at one layer for which a launch counts as such.  In steps of
+// three micro-batches at three layers, 60 + 4 experts, H = 2048, F = 1408, nt
+// loads for items of up to 64 rows take 4 to 5% off at 64 and 96 tokens,
+// nothing at 128, and add 1 to 3% from 192 on; for longer items they gain
+// nothing at any size.
+constexpr int kNtTokens = 128;
+
+template <int BM_, int WM_, int SA_, int SB_, bool NT_ = false>
 struct TileCfg {
+  static constexpr int B_POLICY = NT_ ? kNonTemporal : 0;  // cache policy of the weight loads
   static constexpr int BM = BM_;                 // tile rows
   static constexpr int WM = WM_, WN = kWaves / WM_;  // wavefront grid
   static constexpr int SA = SA_, SB = SB_;       // LDS stages of the A and B rings
@@ -80,6 +93,7 @@ struct TileCfg {
 using CfgBig = TileCfg<256, 2, 2, 3>;
 using CfgMid = TileCfg<128, 2, 3, 3>;
 using CfgSkinny = TileCfg<64, 2, 4, 4>;
+using CfgSkinnyNt = TileCfg<64, 2, 4, 4, true>;
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 constexpr int kLdsElems = cmax(cmax(CfgBig::LDS_ELEMS, CfgMid::LDS_ELEMS), CfgSkinny::LDS_ELEMS);
 static_assert(kLdsElems * 2 <= 160 * 1024, "LDS budget");
@@ -165,17 +179,18 @@ struct Frags {
 // Load j of the wave's A resp. B loads of stage s (K columns 64 s ..
 // 64 s + 63) into A resp. B slot `slot`; issue_a issues all A loads of a stage,
 // issue_b_part a quarter of the B loads.
+template <int POLICY>
 __device__ __forceinline__ void load16_lds(__amdgpu_buffer_rsrc_t r, bf16_t* lds, int voff, int soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds, 16, voff, soff, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds, 16, voff, soff, 0, POLICY);
 }
 template <class C>
 __device__ __forceinline__ void load_a(const KLoop& L, int s, int slot, int j) {
-  load16_lds(L.ra, L.smem + slot * C::A_ELEMS + L.lds_a_load + j * 8 * BK, L.a_lane[j & 1],
+  load16_lds<0>(L.ra, L.smem + slot * C::A_ELEMS + L.lds_a_load + j * 8 * BK, L.a_lane[j & 1],
              (L.a_row0 + 8 * j) * L.row_bytes + s * BK * 2);
 }
 template <class C>
 __device__ __forceinline__ void load_b(const KLoop& L, int s, int slot, int j) {
-  load16_lds(L.rb, L.smem + C::B_RING + slot * C::B_ELEMS + L.lds_b_load + j * 8 * BK, L.b_lane,
+  load16_lds<C::B_POLICY>(L.rb, L.smem + C::B_RING + slot * C::B_ELEMS + L.lds_b_load + j * 8 * BK, L.b_lane,
              L.b_tile + s * L.b_stage + j * 1024);
 }
 template <class C>
@@ -697,6 +712,8 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
       run_item<CfgBig, MODE>(p, smem, A, C, Bbase, row0, row_end, ni, K, ks0, nks, part, wave, lane);
     else if (rows > CfgSkinny::BM)
       run_item<CfgMid, MODE>(p, smem, A, C, Bbase, row0, row_end, ni, K, ks0, nks, part, wave, lane);
+    else if (p.layer_tokens <= kNtTokens)
+      run_item<CfgSkinnyNt, MODE>(p, smem, A, C, Bbase, row0, row_end, ni, K, ks0, nks, part, wave, lane);
     else
       run_item<CfgSkinny, MODE>(p, smem, A, C, Bbase, row0, row_end, ni, K, ks0, nks, part, wave, lane);
     if (tid == 0) *s_next = q.settle(got);
@@ -809,7 +826,8 @@ __global__ __launch_bounds__(64, 1) void stream_gemm_bf16(GroupedProblem p, Weig
                                                0, 0);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, st + (NA + j) * 512, 16, b_voff + j * 1024, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, st + (NA + j) * 512, 16, b_voff + j * 1024, 0, 0,
+                                               kNonTemporal);
     a_soff += BK * 2;
     b_voff += b_stage;
   };
@@ -943,13 +961,14 @@ struct F32Loop {
 // Loads of stage s (K columns 32 s .. 32 s + 31) into ring slot `slot`:
 // wavefront w fills A rows 8 w .. + 7 and its own weight rows.  A row holds
 // eight 16-byte chunks, logical chunk c at c ^ ((row >> 1) & 7).
+template <bool NT>
 __device__ __forceinline__ void f32_issue(const F32Loop& L, int s, int slot) {
   float* st = L.smem + slot * kF32Stage;
   __builtin_amdgcn_raw_ptr_buffer_load_lds(L.ra, st + 8 * L.wave * FBK, 16, L.a_off, s * FBK * 4, 0, 0);
 #pragma unroll
   for (int j = 0; j < 2; ++j)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(L.rb[j], st + (FBM + 16 * L.wave + 8 * j) * FBK, 16, L.b_off[j],
-                                             s * FBK * 4, 0, 0);
+                                             s * FBK * 4, 0, NT ? kNonTemporal : 0);
 }
 
 // K loop over NACT active 16-row blocks.  Lane l reads 16-byte chunk
@@ -957,10 +976,10 @@ __device__ __forceinline__ void f32_issue(const F32Loop& L, int s, int slot) {
 // to MFMA i: every MFMA sums K columns 16 kc + i + {0, 4, 8, 12}, the same
 // order for every row of every item.  The weights are the first operand, so
 // a lane holds four consecutive output columns of one token row.
-template <int NACT>
+template <int NACT, bool NT>
 __device__ __forceinline__ void f32_k_loop(const F32Loop& L, floatx4 (&acc)[FBM / 16]) {
 #pragma unroll
-  for (int s = 0; s < FST - 1; ++s) f32_issue(L, s, s);  // nk >= 4 (K is a multiple of 128)
+  for (int s = 0; s < FST - 1; ++s) f32_issue<NT>(L, s, s);  // nk >= 4 (K is a multiple of 128)
   const int sw = swz(L.lrow, 0), last = L.nk - 1;
   int slot = 0;
   for (int s = 0; s < L.nk; ++s) {
@@ -972,7 +991,7 @@ __device__ __forceinline__ void f32_k_loop(const F32Loop& L, floatx4 (&acc)[FBM 
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
     wait_vm<(FST - 2) * kF32Loads>();
     bar();
-    f32_issue(L, min(s + FST - 1, last), slot == 0 ? FST - 1 : slot - 1);
+    f32_issue<NT>(L, min(s + FST - 1, last), slot == 0 ? FST - 1 : slot - 1);
     const float* st = L.smem + slot * kF32Stage + L.lrow * FBK;
 #pragma unroll
     for (int kc = 0; kc < FBK / 16; ++kc) {
@@ -1052,10 +1071,13 @@ __global__ __launch_bounds__(64 * kF32Waves, kF32Waves * kF32PerCu / 4) void gro
     for (int mb = 0; mb < FBM / 16; ++mb) acc[mb] = (floatx4){0.f, 0.f, 0.f, 0.f};
     const int nact = (rows + 15) >> 4;
     switch (nact) {
-      case 1: f32_k_loop<1>(L, acc); break;
-      case 2: f32_k_loop<2>(L, acc); break;
-      case 3: f32_k_loop<3>(L, acc); break;
-      default: f32_k_loop<4>(L, acc); break;
+      case 1:
+        if (p.layer_tokens <= kNtTokens) f32_k_loop<1, true>(L, acc);
+        else f32_k_loop<1, false>(L, acc);
+        break;
+      case 2: f32_k_loop<2, false>(L, acc); break;
+      case 3: f32_k_loop<3, false>(L, acc); break;
+      default: f32_k_loop<4, false>(L, acc); break;
     }
     // acc[mb][v]: token row 16 mb + lane % 16, weight row 4 (lane / 16) + v.
     // Gate/up: the upper 32 lanes hold the up rows of the lower lanes' gate

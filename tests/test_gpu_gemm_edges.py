@@ -118,6 +118,17 @@ def test_bf16_decode_rows_do_not_depend_on_the_launch(device):
     assert torch.equal(o1.view(torch.int16), o2[:20].view(torch.int16))
 
 
+# items of up to 64 (bf16) and 16 rows (fp32) on both sides of the 128 tokens at
+# a layer up to which their weight loads are non-temporal
+@pytest.mark.parametrize("dtype,row", [("bf16", 40), ("f32", 10)])
+@pytest.mark.parametrize("tokens", [128, 129])
+def test_weight_load_policy(tokens, dtype, row, device):
+    log(f"{dtype} rows {row} of {tokens} tokens")
+    lens, experts = [row, tokens - row], [1, 0]
+    got, ref = _step(device, dtype, 512, 384, 3, 0, lens, experts)
+    _check(got, ref, dtype, f"{tokens} tokens")
+
+
 # fp32 row blocks of 16, m-tiles of 64 sharing a group's rows evenly
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 33, 48, 63, 64, 65, 127, 129, 200, 513])
 def test_f32_group_rows(rows, device):
