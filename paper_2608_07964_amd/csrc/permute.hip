@@ -11,7 +11,8 @@
 //                        it also clears the work counters of the step's
 //                        grouped GEMM launches
 //                        (the three above and perm_scatter_kernel: one launch,
-//                        perm_small_kernel, for steps of up to about 1000 tokens)
+//                        perm_small_kernel, for steps of up to about 1000 tokens,
+//                        with the gather's copies for those of a few)
 //   perm_scatter_kernel  per chunk: stable rank of each pair inside its key from
 //                        per-wavefront 64-bit expert masks (popcount of the lanes
 //                        below), then inv, and perm where a caller asks for it
@@ -277,14 +278,23 @@ constexpr int kSmallPieces = 32;      // pieces of a small step
 constexpr int kSmallSlots = 128;      // pieces x slots of a small step
 constexpr int kSmallWords = 23040;    // LDS words for the pieces' expert masks and counts (90 KB)
 static_assert(EB_MAX_RUN <= kWave, "one lane per entry");
+// Grouped rows of up to kSmallCopy bytes are written here too (row_bytes > 0):
+// a launch less.  One token of 8 slots at H = 2048: step + combine 42.5 ->
+// 41.0 us (another card 41.5 -> 39.8); two tokens 57.0 -> 55.2; from eight on one CU's stores take
+// as long as the launch saved.
+constexpr int kSmallCopy = 128 * 1024;
+constexpr int kSmallRows = kSmallCopy / 512;  // a row has at least 512 bytes (H is a multiple of 256)
+constexpr int kSmallRowPiece = kWave * 16;    // bytes of a row one wavefront copies
 
 template <class RTA>
 __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
     RTA rta, int32_t* __restrict__ offsets, int4* __restrict__ tiles, int bm, TailRule tail, int max_tiles,
-    int32_t* __restrict__ work_ctr, int32_t* __restrict__ perm, int32_t* __restrict__ inv) {
+    int32_t* __restrict__ work_ctr, int32_t* __restrict__ perm, int32_t* __restrict__ inv, int row_bytes,
+    uint8_t* __restrict__ a_perm) {
   __shared__ int running[kMaxKeys];                        // per-key totals, then offsets / cursors
   __shared__ unsigned long long masks[kSmallWords / 2];    // [pieces][E] lanes per expert, then the counts
   __shared__ int wtot[kScanWaves], s_layer[kSmallPieces];
+  __shared__ int s_pos[kSmallRows];                        // inv of a step whose rows are copied here
   const RunTable& rt = rta.get();
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -319,6 +329,20 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   };
   int p_last = -1;         // the piece in tk
   if (wave < np) load(p_last = wave);
+
+  // copy unit u: 1 KB piece u % row_pieces of token u / row_pieces; a
+  // wavefront's first one is read now
+  const int row_pieces = (row_bytes + kSmallRowPiece - 1) / kSmallRowPiece;
+  const int units = rt.tok_base[n] * row_pieces;
+  uint4 row = make_uint4(0, 0, 0, 0);
+  auto read_row = [&](int u) {
+    const int g = u / row_pieces, at = (u - g * row_pieces) * kSmallRowPiece + lane * 16;
+    const int rho = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < n && tok0 + len <= g)));
+    const int t = g - __shfl(tok0, rho, kWave);
+    const uint8_t* src = in_global(static_cast<const uint8_t*>(rt.a[rho])) + (size_t)t * row_bytes;
+    if (at < row_bytes) row = *reinterpret_cast<const uint4*>(src + at);
+  };
+  if (wave < units) read_row(wave);
 
   if (tid < kWorkWords && tid != kWorkTiles && tid != kWorkTiles + 1) work_ctr[tid] = 0;
   for (int i = tid; i < n_keys; i += kScanThreads) running[i] = 0;
@@ -380,7 +404,16 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
                               : cnt[p * ES + E + (r - k)] + lane;
         inv[tk.q0 + r] = pos;
         if (perm) perm[pos] = tk.q0 + r;
+        if (row_bytes > 0) s_pos[tk.q0 + r] = pos;
       }
+  }
+  if (units == 0) return;
+  __syncthreads();
+  for (int u = wave; u < units; u += kScanWaves) {
+    if (u != wave) read_row(u);
+    const int g = u / row_pieces, at = (u - g * row_pieces) * kSmallRowPiece + lane * 16;
+    for (int r = 0; r < slots; ++r)
+      if (at < row_bytes) *reinterpret_cast<uint4*>(a_perm + (size_t)s_pos[g * slots + r] * row_bytes + at) = row;
   }
 }
 
@@ -467,10 +500,10 @@ bool perm_small(const eb_model_desc& d, int pieces) {
 }
 
 template <class RTA>
-void perm_small_impl(RTA a, const StepBuffers& b, int bm, TailRule tail, hipStream_t s) {
+void perm_small_impl(RTA a, const StepBuffers& b, int bm, TailRule tail, int row_bytes, hipStream_t s) {
   prof_start(EB_K_PERM_SCAN, s);
   hipLaunchKernelGGL(perm_small_kernel<RTA>, dim3(1), dim3(kScanThreads), 0, s, a, b.offsets, b.tiles, bm, tail,
-                     b.max_tiles, b.work_ctr, b.perm, b.inv);
+                     b.max_tiles, b.work_ctr, b.perm, b.inv, row_bytes, static_cast<uint8_t*>(b.a_perm));
   prof_stop(EB_K_PERM_SCAN, s);
 }
 
@@ -495,14 +528,17 @@ void permute_impl(RTA a, const eb_model_desc& d, int grid_chunks, int grid_token
                   hipStream_t s) {
   const int bm = gemm_bm(d.dtype);
   const TailRule tail = gemm_tail(d.dtype, d.F);
+  const int elem_bytes = d.dtype == EB_DTYPE_BF16 ? 2 : 4;
   if (perm_small(d, pieces)) {
-    perm_small_impl(a, b, bm, tail, s);
+    const bool copy = (long long)grid_tokens * (d.k + d.S) * d.H * elem_bytes <= kSmallCopy;
+    perm_small_impl(a, b, bm, tail, copy ? d.H * elem_bytes : 0, s);
+    if (copy) return;
   } else {
     perm_count_impl(a, grid_chunks, b.hist, s);
     perm_scan_impl(a, b.hist, b.chunk_base, b.offsets, b.tiles, bm, tail, b.max_tiles, b.work_ctr, s);
     perm_scatter_impl(a, grid_chunks, b.chunk_base, b.perm, b.inv, s);
   }
-  gather_impl(a, d.H, grid_tokens, d.dtype == EB_DTYPE_BF16 ? 2 : 4, b.inv, b.a_perm, s);
+  gather_impl(a, d.H, grid_tokens, elem_bytes, b.inv, b.a_perm, s);
 }
 
 bool scan_fits(int L, int E, int S, int n) {

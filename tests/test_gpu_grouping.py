@@ -11,10 +11,14 @@ from oracle import permute as operm
 pytestmark = pytest.mark.gpu
 
 
-# name: (dtype, L, E, S, k, tokens of each entry); layers cycle, so one layer's
+# name: (dtype, L, E, S, k, tokens of each entry[, H]); layers cycle, so one layer's
 # entries are not neighbours
 CASES = {
     "one_token": ("bf16", 1, 64, 2, 6, [1]),
+    "one_token_wide": ("bf16", 1, 64, 1, 8, [1], 7168),      # 126 KB of rows: copied by the same launch
+    "copy_full": ("bf16", 2, 8, 0, 2, [1, 0, 41], 768),      # 84 rows of 1.5 KB: 126 KB; 88 rows: 132 KB
+    "copy_over": ("bf16", 2, 8, 0, 2, [1, 0, 43], 768),
+    "copy_f32": ("f32", 2, 8, 1, 2, [3, 6], 1024),
     "piece_edges": ("bf16", 2, 60, 4, 4, [63, 64, 65, 0, 127, 128, 129, 1]),
     "many_entries": ("bf16", 5, 8, 0, 2, [1 + i % 7 for i in range(32)]),
     "64_entries": ("bf16", 5, 8, 0, 2, [1 + i % 7 for i in range(64)]),
@@ -34,8 +38,8 @@ CASES = {
 def test_grouping(name, device):
     from paper_2608_07964_amd import binding as B
     log(f"grouping {name}")
-    dtype, L, E, S, k, lens = CASES[name]
-    H, F = 256, 128
+    dtype, L, E, S, k, lens, *rest = CASES[name]
+    H, F = rest[0] if rest else 256, 128
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     rng = np.random.default_rng(11)
     g = torch.Generator(device=device).manual_seed(11)
