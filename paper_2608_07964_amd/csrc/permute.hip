@@ -279,8 +279,8 @@ constexpr int kSmallSlots = 128;      // pieces x slots of a small step
 constexpr int kSmallWords = 23040;    // LDS words for the pieces' expert masks and counts (90 KB)
 static_assert(EB_MAX_RUN <= kWave, "one lane per entry");
 // Grouped rows of up to kSmallCopy bytes are written here too (row_bytes > 0):
-// a launch less.  One token of 8 slots at H = 2048: step + combine 42.5 ->
-// 41.0 us (another card 41.5 -> 39.8); two tokens 57.0 -> 55.2; from eight on one CU's stores take
+// a launch less.  One token of 8 slots at H = 2048: step + combine 41.5 ->
+// 39.8 us; two tokens 57.0 -> 55.2; from eight tokens on one CU's stores take
 // as long as the launch saved.
 constexpr int kSmallCopy = 128 * 1024;
 constexpr int kSmallRows = kSmallCopy / 512;  // a row has at least 512 bytes (H is a multiple of 256)

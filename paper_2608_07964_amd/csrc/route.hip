@@ -7,9 +7,9 @@
 //   route_mfma_kernel /  the matrix cores and the top-k of the workgroup's 32
 //   route_lds_kernel     tokens from an LDS logit tile (E <= 64: 32 tokens,
 //                        split-K over the 4 wavefronts, operands straight into
-//                        registers; E > 64: 128 tokens, 8 wavefronts splitting
-//                        tokens and experts, operands staged through LDS as
-//                        whole cache lines)
+//                        registers; E > 64: 128 tokens, or 32 in launches of up
+//                        to 8192, wavefronts splitting tokens and experts,
+//                        operands staged through LDS as whole cache lines)
 //   RMSNorm +            other fp32 stacks: RMSNorm, an LDS-tiled fp32
 //   logits_kernel +      VALU GEMM for z, then the top-k
 //   topk_kernel
