@@ -736,11 +736,11 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
 // Each output is the same chain of MFMAs as in grouped_gemm_bf16, bit for bit.
 //
 // Bound by HBM: 74 groups of 2 to 31 rows at H = 2048, F = 1408 stream their
-// weights at 5.7 (gate/up, 149 us) and 5.5 TB/s (down, 76 us), against 162 and
-// 87 us in 256-column items on whole-CU workgroups; one token with 8 expert
-// slots 18 and 11 against 28 and 21 us (four times the units, so every CU
-// has some).  Five wavefronts of 32 KB per CU, three of 53 KB or two of 80 KB
-// measured 0 to 5% slower.
+// weights at 6.4 (gate/up, 133 us) and 6.0 TB/s (down, 69 us), 149 and 76 us
+// without the nt policy, against 162 and 87 us in 256-column items on whole-CU
+// workgroups; one token with 8 expert slots 16 and 10 against 28 and 21 us
+// (four times the units, so every CU has some).  Five wavefronts of 32 KB per
+// CU, three of 53 KB or two of 80 KB measured 0 to 5% slower.
 constexpr int kStreamLds = 40 * 1024, kStreamPerCu = 4;
 template <int NA>
 struct StreamCfg {
