@@ -738,7 +738,7 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_bf16(GroupedProblem 
 // Bound by HBM: 74 groups of 2 to 31 rows at H = 2048, F = 1408 stream their
 // weights at 6.4 (gate/up, 133 us) and 6.0 TB/s (down, 69 us), 149 and 76 us
 // without the nt policy, against 162 and 87 us in 256-column items on whole-CU
-// workgroups; one token with 8 expert slots 16 and 10 against 28 and 21 us
+// workgroups; one token with 8 expert slots 16 and 12 against 28 and 21 us
 // (four times the units, so every CU has some).  Five wavefronts of 32 KB per
 // CU, three of 53 KB or two of 80 KB measured 0 to 5% slower.
 constexpr int kStreamLds = 40 * 1024, kStreamPerCu = 4;
