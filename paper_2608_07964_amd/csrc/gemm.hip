@@ -618,13 +618,28 @@ __device__ __forceinline__ Tile2 item_tile(int local, int mt, int n_ntiles) {
 // launch ends on short items.  They are split into eighths like the others
 // (drawn by all XCDs from one counter, every XCD streamed from every expert:
 // a launch of 256 items of K = 7168 took 220 instead of 158 us).
+//
+// A split-K launch has few, long items (32 per m-tile, of K = 7168, at
+// H = 4096, F = 14336), and those of a small group, bound by streaming their
+// weights, are hardly shorter than the others: they overlap better with the
+// others' matrix work than with each other.  Setting them aside pays there only
+// where the last round of items would leave most workgroups idle, or where all
+// fit one round (every XCD then has some of them); else they stay in the queue.
+// Down launch of 8 experts, 2 picks a token, in us, always set aside / by this
+// rule / never: 2.0 rounds (128 tokens at each of two layers) 356 / 308 / 315;
+// 4.0 rounds (64 at each of four) 646 / 583 / 603; 1.12 rounds (512 at one)
+// 227 / 229 / 343; 2.25 rounds (384 at each of two) 437 / 438 / 480.
 struct ItemQueue {
   int32_t* ctr;
   long long main;  // items before the ones set aside
   int total, xcd, victim, per_xcd;  // victim: XCD range drawn from, + kXcds for its set-aside range
   __device__ __forceinline__ ItemQueue(const GroupedProblem& p, int nsub)
-      : ctr(p.work_ctr), main((long long)p.n_tiles[1] * nsub), total(p.n_tiles[0] * nsub), xcd(blockIdx.x % kXcds),
-        victim(blockIdx.x % kXcds), per_xcd(gridDim.x / kXcds) {}
+      : ctr(p.work_ctr), total(p.n_tiles[0] * nsub), xcd(blockIdx.x % kXcds), victim(blockIdx.x % kXcds),
+        per_xcd(gridDim.x / kXcds) {
+    const int last = total % (int)gridDim.x;  // items of the last, partial round
+    const bool aside = p.ksplit == 1 || total <= (int)gridDim.x || (last > 0 && 2 * last <= (int)gridDim.x);
+    main = aside ? (long long)p.n_tiles[1] * nsub : total;
+  }
   __device__ __forceinline__ int bound(int x) const {  // first item of range x; bound(2 kXcds) = total
     return x < kXcds ? (int)((x * main) / kXcds) : (int)(main + ((x - kXcds) * (total - main)) / kXcds);
   }
@@ -1169,17 +1184,23 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
 
 int gemm_bm(int dtype) { return dtype == EB_DTYPE_BF16 ? BM : FBM; }
 
-// Row blocks to set aside for the end of a launch (see ItemQueue): about one
-// and a half items per workgroup, from groups of up to half a tile, whose
-// items take half as long as a full tile's.  Without them the workgroups
-// ended up to one long item apart: 44700 rows in 128 groups at H = 2048,
-// F = 1408 700 -> 597 us (gate/up) and 380 -> 327 us (down) on one box, steps
-// of 128-token micro-batches 218 -> 211 and 126 -> 116 us; a third fewer or
-// more measure the same.  fp32 items are short as they are (no gain).
+// Row blocks to set aside for the end of a launch (see ItemQueue): one and a
+// half gate/up items per workgroup (the down launch has the same list: 1.1
+// items at H = 2048, F = 1408, 2.6 at H = 7168, F = 2048), from groups of up to
+// half a tile, whose items take half as long as a full tile's.  Without them
+// the workgroups ended up to one long item apart: gate/up of 8192 tokens on
+// 256 experts of H = 7168, F = 2048 4050 -> 3990 us (its down launch gains
+// nothing from them), of three 512-token micro-batches on 8 experts of
+// H = 4096, F = 14336 940 -> 920 us.  fp32 items are short as they are (no
+// gain).  Where the down launch splits K, only groups of the 64-row tile shape:
+// a 65- to 128-row item of K = 7168 is nearly as long as a full tile's, and ends
+// the launch late (768 tokens on those 8 experts, down launch 363 us with
+// them, 346 without; a whole pass of that stack, its nine down launches 4.93
+// ms, 4.66 with the rule of ItemQueue as well).
 TailRule gemm_tail(int dtype, int F) {
   if (dtype != EB_DTYPE_BF16) return TailRule{0, 0};
   const int nsub = F / (BN / 2);
-  return TailRule{(384 + nsub - 1) / nsub, BM / 2};
+  return TailRule{(384 + nsub - 1) / nsub, down_ksplit(dtype, F) > 1 ? CfgSkinny::BM : BM / 2};
 }
 
 hipError_t launch_pack_weights(int dtype, int gateup, int n, int N, int K, int F, const void* src,

@@ -129,6 +129,22 @@ def test_weight_load_policy(tokens, dtype, row, device):
     _check(got, ref, dtype, f"{tokens} tokens")
 
 
+# Small groups set aside for the end of a launch, every row of every group
+# checked.  K in one part: 64 small groups against the 35 that F = 1408 sets
+# aside.  Split K (8 down items a group here, on 256 workgroups): one round
+# exactly, a last round of 8 items, of half the workgroups and of 8 more, and
+# two rounds exactly -- set aside in the first three only.
+@pytest.mark.parametrize("H,F,groups", [(256, 1408, 64), (1024, 8192, 32), (1024, 8192, 33), (1024, 8192, 48),
+                                        (1024, 8192, 49), (1024, 8192, 64)])
+def test_bf16_groups_set_aside(H, F, groups, device):
+    log(f"bf16 set aside H {H} F {F} groups {groups}")
+    # rows of the 64- and 128-row tile shapes and a few of the 256-row shape
+    lens = [(1 + 7 * i) % 64 + 1 if i % 4 else 65 + (29 * i) % 64 for i in range(groups)]
+    lens[5], lens[groups - 2] = 129, 256
+    got, ref = _step(device, "bf16", H, F, groups, 0, lens, [(5 * i) % groups if groups % 5 else i for i in range(groups)])
+    _check(got, ref, "bf16", f"{groups} groups")
+
+
 # fp32 row blocks of 16, m-tiles of 64 sharing a group's rows evenly
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 33, 48, 63, 64, 65, 127, 129, 200, 513])
 def test_f32_group_rows(rows, device):
