@@ -22,6 +22,8 @@
 //
 // Pair q = (tok_base[rho] + t) * (k+S) + r; key = layer*(E+S) + slot expert.
 // All results are integers fixed by the inputs (no order-dependent atomics).
+#include <type_traits>
+
 #include "eb_internal.h"
 #include "eb_numeric.h"
 
@@ -269,7 +271,10 @@ __global__ __launch_bounds__(kPermChunk) void perm_scatter_kernel(
 // launches above each take about 5 us for a step of a few hundred tokens
 // whatever they do, one after the other; here the pairs of 64 tokens at a time
 // (a piece, one token per lane) are counted in LDS, scanned and placed without
-// leaving the CU.  The same integers as the three kernels give.
+// leaving the CU.  The same integers as the three kernels give, also for a
+// token that picks an expert more than once (a caller's picks may): such pairs
+// share the token's row, one for each token of a kPermChunk-token chunk, and
+// the next chunk starts after all the pairs counted.
 // It costs about 7 us plus 65 ns per slot of a piece (LDS atomics, then
 // scattered stores, all from one CU): 16 pieces of 8 slots over 64 experts 15
 // us against 17 (5 + 7 + 5) for the three launches, 32 pieces of 8 slots 24 us
@@ -294,6 +299,7 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   __shared__ int running[kMaxKeys];                        // per-key totals, then offsets / cursors
   __shared__ unsigned long long masks[kSmallWords / 2];    // [pieces][E] lanes per expert, then the counts
   __shared__ int wtot[kScanWaves], s_layer[kSmallPieces];
+  __shared__ bool s_head[kSmallPieces], s_repeat;          // the piece starts a chunk; some token repeats a pick
   __shared__ int s_pos[kSmallRows];                        // inv of a step whose rows are copied here
   const RunTable& rt = rta.get();
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -315,12 +321,14 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   // this lane's token of piece p and its picks
   struct Token {
     int rho, q0, rows;     // entry, first pair, tokens of the piece
+    bool head;
     int e[kMaxSlots];
   } tk;
   auto load = [&](int p) {
     tk.rho = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < n && upto <= p)));
     const int t0 = (p - __shfl(upto - own, tk.rho, kWave)) * kWave;
     tk.rows = min(kWave, __shfl(len, tk.rho, kWave) - t0);
+    tk.head = t0 % kPermChunk == 0;
     tk.q0 = (__shfl(tok0, tk.rho, kWave) + t0 + lane) * slots;
     const int32_t* ix = in_global(rt.idx[tk.rho]) + (size_t)(t0 + lane) * k;
 #pragma unroll
@@ -345,13 +353,17 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   if (wave < units) read_row(wave);
 
   if (tid < kWorkWords && tid != kWorkTiles && tid != kWorkTiles + 1) work_ctr[tid] = 0;
+  if (tid == 0) s_repeat = false;
   for (int i = tid; i < n_keys; i += kScanThreads) running[i] = 0;
   for (int i = tid; i < np * E; i += kScanThreads) masks[i] = 0ull;
   for (int i = tid; i < np * ES; i += kScanThreads) cnt[i] = 0;
   __syncthreads();
   for (int p = wave; p < np; p += kScanWaves) {
     if (p != p_last) load(p_last = p);
-    if (lane == 0) s_layer[p] = rt.layer[tk.rho];
+    if (lane == 0) {
+      s_layer[p] = rt.layer[tk.rho];
+      s_head[p] = tk.head;
+    }
     if (lane < S) cnt[p * ES + E + lane] = tk.rows;
 #pragma unroll
     for (int r = 0; r < kMaxSlots; ++r)
@@ -362,36 +374,43 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   }
   __syncthreads();
   for (int i = tid; i < np * ES; i += kScanThreads) {
-    const int p = i / ES;
+    const int p = i / ES, c = i - p * ES;
     const int v = cnt[i];
-    if (v) atomicAdd(&running[s_layer[p] * ES + i - p * ES], v);
+    if (v) atomicAdd(&running[s_layer[p] * ES + c], v);
+    if (v > 1 && c < E && __popcll(masks[p * E + c]) != v) s_repeat = true;
   }
   __syncthreads();
   offsets_and_tiles(running, n_keys, wtot, offsets, tiles, bm, tail, max_tiles, work_ctr);
   // first position of every (piece, column): the pieces in order
-  for (int c = tid; c < ES; c += kScanThreads) {
-    int layer = -1, cur = 0;
-    for (int p0 = 0; p0 < np; p0 += 8) {
-      int v[8], l[8];  // read ahead of the stores
+  auto first_positions = [&](auto repeats) {
+    for (int c = tid; c < ES; c += kScanThreads) {
+      int layer = -1, cur = 0, at = 0;
+      for (int p0 = 0; p0 < np; p0 += 8) {
+        int v[8], l[8];  // read ahead of the stores
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (p0 + j < np) {
-          v[j] = cnt[(p0 + j) * ES + c];
-          l[j] = s_layer[p0 + j];
-        }
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (p0 + j < np) {
-          if (l[j] != layer) {
-            if (layer >= 0) running[layer * ES + c] = cur;
-            cur = running[l[j] * ES + c];
-            layer = l[j];
+        for (int j = 0; j < 8; ++j)
+          if (p0 + j < np) {
+            v[j] = cnt[(p0 + j) * ES + c];
+            l[j] = s_layer[p0 + j];
           }
-          cnt[(p0 + j) * ES + c] = cur;
-          cur += v[j];
-        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (p0 + j < np) {
+            if (l[j] != layer) {
+              if (layer >= 0) running[layer * ES + c] = cur;
+              cur = running[l[j] * ES + c];
+              layer = l[j];
+            }
+            if (!repeats || s_head[p0 + j]) at = cur;
+            cnt[(p0 + j) * ES + c] = at;
+            if (repeats) at += c < E ? __popcll(masks[(p0 + j) * E + c]) : v[j];
+            cur += v[j];
+          }
+      }
     }
-  }
+  };
+  if (s_repeat) first_positions(std::true_type{});
+  else first_positions(std::false_type{});
   __syncthreads();
   for (int p = p_last; p >= 0; p -= kScanWaves) {
     if (p != p_last) load(p);

@@ -72,3 +72,41 @@ def test_grouping(name, device):
     rows = torch.from_numpy(perm // (k + S)).to(device)
     assert torch.equal(v["a_perm"], src[rows])
     assert not o.any()                               # zero experts: every row was computed
+
+
+@pytest.mark.parametrize("T", [65, 200, 600])
+def test_grouping_of_repeated_picks(T, device):
+    """Tokens that pick an expert twice (or ids outside [0, E), clamped) alone, grouped
+    by the one-workgroup kernel, and before 2100 tokens of another layer, grouped by the
+    three launches: the same positions, and each pair's position holds its token's row."""
+    from paper_2608_07964_amd import binding as B
+    log(f"repeated picks T {T}")
+    H, F, E, k, L, T2 = 256, 128, 5, 3, 2, 2100
+    g = torch.Generator(device=device).manual_seed(T)
+    idx = torch.randint(-1, E + 1, (T, k), generator=g, device=device, dtype=torch.int32)
+    idx2 = torch.randint(0, E, (T2, k), generator=g, device=device, dtype=torch.int32)
+    a = torch.randn(T, H, generator=g, device=device).bfloat16()
+    a2 = torch.randn(T2, H, generator=g, device=device).bfloat16()
+    w = torch.ones(T2, k, device=device)
+    gu = [torch.zeros(E, 2 * F, H, dtype=torch.bfloat16, device=device) for _ in range(L)]
+    dn = [torch.zeros(E, H, F, dtype=torch.bfloat16, device=device) for _ in range(L)]
+    desc = B.make_desc(L, H, F, E, k, 0, 1, "bf16")
+    pos = []
+    for ents in ([(0, 0, T, a, idx, w)], [(0, 0, T, a, idx, w), (1, 1, T2, a2, idx2, w)]):
+        P = sum(e[2] for e in ents) * k
+        o = torch.empty(P, H, dtype=torch.bfloat16, device=device)
+        inv = torch.full((P,), -1, dtype=torch.int32, device=device)
+        v = dict(a_perm=torch.zeros(P, H, dtype=torch.bfloat16, device=device),
+                 offsets=torch.full((L * E + 1,), -1, dtype=torch.int32, device=device))
+        wsb = B.easybalance_moe_step_workspace_size(desc, [e[2] for e in ents])
+        ws = torch.empty(wsb + 256, dtype=torch.uint8, device=device)
+        B.easybalance_moe_step(desc, B.work_array(ents), len(ents), gu, dn, ws.data_ptr() + (-ws.data_ptr()) % 256,
+                               wsb, o, inv, v)
+        torch.cuda.synchronize()
+        p = inv[:T * k].long()
+        key = idx.clamp(0, E - 1).reshape(-1).long()
+        assert ((p >= v["offsets"][key]) & (p < v["offsets"][key + 1])).all()
+        assert torch.equal(v["a_perm"][p], a.repeat_interleave(k, 0))
+        pos.append((p, v["offsets"][:E + 1]))
+    assert torch.equal(pos[0][1], pos[1][1])
+    assert torch.equal(pos[0][0], pos[1][0])
