@@ -75,7 +75,11 @@ extern "C" {
 #define EB_MAX_RUN 64
 #define EB_MAX_LAYERS 128
 
-/* Kernel classes reported by the profiling calls. */
+/* Kernel classes reported by the profiling calls.  A call reports the classes
+ * of the kernels it launches: a router that also picks (fused or matrix-core)
+ * is ROUTE_LOGITS, and ROUTE_TOPK its separate top-k and count launches, none
+ * where the router counts too; the grouping of a small step runs as one
+ * kernel, reported as PERM_SCAN (with the gather's copies in the smallest). */
 #define EB_K_ROUTE_NORM 0
 #define EB_K_ROUTE_LOGITS 1
 #define EB_K_ROUTE_TOPK 2

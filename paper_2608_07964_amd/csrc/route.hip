@@ -1052,7 +1052,6 @@ template <class RBA>
 void route_halves_launch(const eb_model_desc& d, RBA rba, int grid, hipStream_t s) {
   hipLaunchKernelGGL((route_lds_kernel<RouteTile32x128, false, true, RBA>), dim3(grid, 2),
                      dim3(64 * RouteTile32x128::WAVES), 0, s, rba, d.H, d.E, d.k, d.norm_topk);
-  hipLaunchKernelGGL((topk_rows_kernel<8, RBA>), dim3(grid), dim3(256), 0, s, rba, d.E, d.k, d.norm_topk);
 }
 
 // grid_entries / grid_tokens / grid_blocks: entries, tokens and 32-token
@@ -1066,7 +1065,7 @@ hipError_t route_batch_typed(const eb_model_desc& d, RBA rba, const RouteBatch* 
   // the matrix-core routers count an entry's picks themselves where one
   // workgroup holds the whole entry
   const bool halves = z_stored && d.E > 128 && grid_tokens <= kRouteHalvesTokens;
-  const bool own = !halves && sizeof(TA) == 2 && one_block && !fused_token_path<TA>(d) && grid_tokens <= kRouteWideTokens;
+  const bool own = !halves && sizeof(TA) == 2 && one_block && !fused_token_path<TA>(d);
   if (grid_tokens > 0) {
     if (fused_token_path<TA>(d)) {
       prof_start(EB_K_ROUTE_LOGITS, s);
@@ -1113,6 +1112,11 @@ hipError_t route_batch_typed(const eb_model_desc& d, RBA rba, const RouteBatch* 
           own ? route_lds_launch<RouteTile32x256, true>(d, rba, grid_blocks, s)
               : route_lds_launch<RouteTile32x256, false>(d, rba, grid_blocks, s);
         prof_stop(EB_K_ROUTE_LOGITS, s);
+        if (halves) {
+          prof_start(EB_K_ROUTE_TOPK, s);
+          hipLaunchKernelGGL((topk_rows_kernel<8, RBA>), dim3(grid_blocks), dim3(256), 0, s, rba, d.E, d.k, d.norm_topk);
+          prof_stop(EB_K_ROUTE_TOPK, s);
+        }
       } else {
         if (host_rb == nullptr) return hipErrorInvalidValue;
         const RouteBatch& rb = *host_rb;
@@ -1137,10 +1141,11 @@ hipError_t route_batch_typed(const eb_model_desc& d, RBA rba, const RouteBatch* 
       }
     }
   }
-  prof_start(EB_K_ROUTE_TOPK, s);
-  if (grid_entries > 0 && !own)
+  if (grid_entries > 0 && !own) {
+    prof_start(EB_K_ROUTE_TOPK, s);
     hipLaunchKernelGGL((counts_kernel<RBA>), dim3(grid_entries), dim3(1024), 0, s, rba, d.k, d.E);
-  prof_stop(EB_K_ROUTE_TOPK, s);
+    prof_stop(EB_K_ROUTE_TOPK, s);
+  }
   return hipGetLastError();
 }
 

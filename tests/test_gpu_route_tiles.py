@@ -2,8 +2,9 @@
 token counts at the edges of their 32- and 128-token tiles, expert counts of
 every kernel choice, with and without stored logits (bf16, through the C ABI).
 
-A logit is one chain of matrix instructions over K whichever tile its token is
-in, so a token routed alone gives the bits it gives in any batch."""
+A logit is summed in one order whichever tile its token is in (E > 64: one chain
+of matrix instructions over K; else the sums of four K quarters, added in
+order), so a token routed alone gives the bits it gives in any batch."""
 import numpy as np
 import pytest
 import torch
@@ -60,3 +61,21 @@ def test_route_tiles(E, k, H, device):
                     got, want = got.view(torch.int16), want.contiguous().view(torch.int16)
                 assert torch.equal(got, want), (key, T, want_z)
             assert torch.equal(o["counts"].long(), torch.bincount(ref["idx"][:T].reshape(-1).long(), minlength=E))
+
+
+# (E, T, stored logits) -> launches of the router and of separate top-k and count kernels
+@pytest.mark.parametrize("E,T,want_z,logits,topk", [(64, 32, True, 1, 0), (64, 33, True, 1, 1), (100, 16, True, 1, 0),
+                                                    (256, 16, False, 1, 0), (256, 16, True, 1, 2), (256, 64, False, 1, 1)])
+def test_profile_counts_the_launches(E, T, want_z, logits, topk, device):
+    from paper_2608_07964_amd import binding as B
+    log(f"profile E {E} T {T} z {want_z}")
+    H, k = 256, 4
+    g = torch.Generator(device=device).manual_seed(1)
+    desc = B.make_desc(1, H, 128, E, k, 0, 1, "bf16")
+    B.easybalance_profile_begin()
+    _route(B, desc, torch.randn(T, H, generator=g, device=device), torch.ones(H, device=device),
+           torch.randn(E, H, generator=g, device=device).bfloat16(), torch.zeros(E, device=device), T, want_z)
+    torch.cuda.synchronize()
+    p = B.easybalance_profile_end()
+    assert (p["route_norm"][1], p["route_logits"][1], p["route_topk"][1]) == (1, logits, topk)
+    assert (p["route_topk"][0] > 0) == (topk > 0)
