@@ -118,8 +118,9 @@ typedef struct eb_work {
   const float* w;       /* [T][k] routing weights                        */
 } eb_work;
 
-/* Optional extra outputs of easybalance_moe_step (any member may be NULL;
- * a NULL member lives in the workspace instead).  P = sum_rho T_rho * (k+S). */
+/* Optional extra outputs of easybalance_moe_step (any member may be NULL: a
+ * NULL a_perm, h or offsets lives in the workspace instead, a NULL perm is
+ * not produced).  P = sum_rho T_rho * (k+S). */
 typedef struct eb_step_views {
   void* a_perm;         /* [P][H] dtype: rows grouped by (layer, expert)  */
   void* h;              /* [P][F] dtype: SwiGLU activations               */
@@ -257,7 +258,9 @@ int easybalance_moe_step_workspace_size(const eb_model_desc* desc, int32_t n_run
  * o_out    device [P][H] dtype: expert outputs at grouped positions
  * inv_out  device [P] int32: grouped position of pair q
  * views    host pointer to optional outputs (nullable)
- * Expert ids outside [0, E) in idx are clamped into range (no fault).
+ * Expert ids outside [0, E) in idx are clamped into range (no fault).  Slots
+ * in which a token picks the same expert share one grouped position (the same
+ * result); its group counts every pair, and rows no pair maps to are unspecified.
  * A step whose entries all have T = 0 (P = 0) enqueues nothing and writes
  * no output, views->offsets included; the weight and output pointers are
  * then not checked.
@@ -272,9 +275,9 @@ int easybalance_moe_step(const eb_model_desc* desc, int32_t n_run, const eb_work
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same kernels, same results bit for bit;
  * the call allocates nothing (no hipMalloc/hipFree, no host heap).  The step's
- * scratch -- permutation histograms and bases, tile and group lists, work
- * counters, perm and offsets unless views supplies them, and for long K
- * (bf16, F >= 8192) the two fp32 partial-sum planes 2 * P * H * 4 bytes --
+ * scratch -- permutation histograms and bases, the tile list, work counters,
+ * offsets unless views supplies them, and for long K (bf16, F >= 8192) the
+ * two fp32 partial-sum planes 2 * P * H * 4 bytes --
  * sits in a static device array of EB_NOALLOC_SCRATCH_BYTES that the library
  * holds on every device it runs on until the process ends.
  *

@@ -87,7 +87,6 @@ WsLayout ws_layout(const eb_model_desc& d, const StepShape& s, const eb_step_vie
   w.tiles = take(sizeof(int4) * (size_t)(s.max_tiles > 0 ? s.max_tiles : 1));
   w.work_ctr = take(sizeof(int32_t) * kWorkWords);
   w.partial = down_ksplit(d.dtype, d.F) > 1 ? take(sizeof(float) * 2 * (size_t)s.P * d.H) : 0;
-  if (!(v && v->perm)) take(sizeof(int32_t) * (size_t)s.P);  // not written; part of the published size
   w.a_perm = (v && v->a_perm) ? 0 : take(eb * (size_t)s.P * d.H);
   w.h = (v && v->h) ? 0 : take(eb * (size_t)s.P * d.F);
   w.total = off;
@@ -181,7 +180,6 @@ int run_gemms(const eb_model_desc& d, const StepShape& sh, const StepWs& w, cons
   gp.E = d.E;
   gp.S = d.S;
   gp.P = (int32_t)sh.P;
-  gp.offsets = w.b.offsets;
   gp.P_live = w.b.offsets + (size_t)d.L * (d.E + d.S);
   gp.tiles = w.b.tiles;
   gp.n_tiles = w.b.work_ctr + kWorkTiles;

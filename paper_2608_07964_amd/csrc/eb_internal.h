@@ -51,14 +51,15 @@ struct GroupedProblem {
   int32_t H, F, E, S;                      // E+S expert slots per layer
   int32_t P;                               // grouped rows the buffers hold (the live
                                            // rows or, device-scheduled, the largest step's)
-  const int32_t* offsets;                  // [L*(E+S)+1]
   const int32_t* P_live;                   // device scalar: the live grouped rows
                                            // (offsets[L*(E+S)])
   const int4* tiles;                       // [n_tiles] the row block's group: (key, first row,
                                            // rows, index of the group's first row block)
   const int32_t* n_tiles;                  // device [2]: row blocks over all groups, and how many
                                            // of them come before those set aside for the end
-  int32_t layer_tokens;                    // the most tokens the step has at one layer
+  int32_t layer_tokens;                    // bound of the tokens the step has at one layer: the most at
+                                           // one (easybalance_moe_step), all micro-batches' (a device-
+                                           // scheduled pass, whose layers the host does not know)
   int32_t* work_ctr;                       // per-XCD work counters of this launch, zeroed:
                                            // XCD x's at work_ctr[x * kWorkStride]
   int32_t ksplit;                          // 1, or 2: K halves computed by separate items

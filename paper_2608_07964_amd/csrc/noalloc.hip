@@ -1,8 +1,8 @@
 // easybalance_moe_step_noalloc: easybalance_moe_step for callers that cannot
 // allocate device memory.  The step's scratch (permutation histograms and
-// bases, key offsets, tile and group lists, work counters, perm, the split-K
-// partial sums) lives in a file-scope device array instead of a caller
-// workspace; the kernels are the same, so the results are the same bits.
+// bases, key offsets, the tile list, work counters, the split-K partial sums)
+// lives in a file-scope device array instead of a caller workspace; the
+// kernels are the same, so the results are the same bits.
 //
 // In host code `scratch` names a host-side stand-in, not device memory: the
 // array's device address is taken once per device with hipGetSymbolAddress

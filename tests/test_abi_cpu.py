@@ -117,6 +117,11 @@ def test_workspace_size_and_desc_checks():
     P = 4 * 512 * 2
     assert ws >= P * 4096 * 2 + P * 14336 * 2
     assert ws % 256 == 0
+    # the grouped rows, the activations and small tables; no perm (4 P bytes) that nothing would read
+    d16 = B.make_desc(1, 256, 128, 8, 8, 8, 1, "bf16")
+    P = 40960 * 16
+    rows = P * (256 + 128) * 2
+    assert rows <= B.easybalance_moe_step_workspace_size(d16, [40960]) < rows + 2 * P
     for bad, code in [(B.make_desc(8, 4000, 14336, 8, 2, 0, 8, "bf16"), B.EB_ERR_UNSUPPORTED),
                       (B.make_desc(8, 4096, 14300, 8, 2, 0, 8, "bf16"), B.EB_ERR_UNSUPPORTED),
                       (B.make_desc(8, 4096, 14336, 8, 9, 0, 8, "bf16"), B.EB_ERR_INVALID_ARG),

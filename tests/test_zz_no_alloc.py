@@ -78,8 +78,8 @@ def test_noalloc_matches_workspace_entry_point(cfg, device):
         wsp = ws.data_ptr() + (-ws.data_ptr()) % 256
         o_ref, inv_ref, v_ref = _outputs(cfg, P, device)
         B.easybalance_moe_step(desc, run, len(ents), inp.W_gu, inp.W_dn, wsp, ws_bytes, o_ref, inv_ref, v_ref)
-        # no-alloc entry point: perm and offsets in the static scratch on the
-        # first call, in the caller's views on the second
+        # no-alloc entry point: offsets in the static scratch and no perm on the
+        # first call, both in the caller's views on the second
         o, inv, v = _outputs(cfg, P, device)
         if call == 0:
             v_pass = dict(a_perm=v["a_perm"], h=v["h"])
