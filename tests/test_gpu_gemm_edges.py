@@ -13,21 +13,24 @@ from gpu_helpers import assert_close, log
 pytestmark = pytest.mark.gpu
 
 
-def _step(device, dtype, H, F, E, S, lens, experts, seed=3):
+def _step(device, dtype, H, F, E, S, lens, experts, seed=3, spoil=None):
     """One layer of E routed (top-1) and S shared experts; micro-batch i's tokens all pick
-    experts[i].  Returns (o, h, a_perm) of the step and their float64 values."""
+    experts[i].  spoil(gu, dn, rows): changes the weights or the micro-batches' rows first.
+    Returns (o, h, a_perm) of the step and their float64 values."""
     from paper_2608_07964_amd import binding as B
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     g = torch.Generator(device=device).manual_seed(seed)
     gu = (torch.randn(E + S, 2 * F, H, generator=g, device=device) * 0.05).to(tdt)
     dn = (torch.randn(E + S, H, F, generator=g, device=device) * 0.05).to(tdt)
+    acts = [torch.randn(T, H, generator=g, device=device).to(tdt) for T in lens]
+    if spoil:
+        spoil(gu, dn, acts)
     desc = B.make_desc(1, H, F, E, 1, S, 1, dtype)
     pgu, pdn = torch.empty_like(gu), torch.empty_like(dn)
     B.easybalance_pack_weights(desc, B.EB_WEIGHTS_GATE_UP, E + S, gu, pgu)
     B.easybalance_pack_weights(desc, B.EB_WEIGHTS_DOWN, E + S, dn, pdn)
     ents = []
-    for i, (T, e) in enumerate(zip(lens, experts)):
-        a = torch.randn(T, H, generator=g, device=device).to(tdt)
+    for i, (T, e, a) in enumerate(zip(lens, experts, acts)):
         ents.append((i, 0, T, a, torch.full((T, 1), e, dtype=torch.int32, device=device),
                      torch.ones(T, 1, device=device)))
     P = sum(lens) * (1 + S)
@@ -57,7 +60,7 @@ def _step(device, dtype, H, F, E, S, lens, experts, seed=3):
 
 
 def _check(got, ref, dtype, what):
-    for g, r, n in zip(got, ref, ("o", "h", "a_perm")):
+    for g, r, n in zip(got, ref, ("o", "h", "a_perm")[-len(got):]):
         assert_close(g.float().cpu().numpy(), r.float().cpu().numpy(), dtype, f"{what} {n}")
 
 
@@ -159,3 +162,50 @@ def test_f32_shapes(H, F, device):
     log(f"f32 H {H} F {F}")
     got, ref = _step(device, "f32", H, F, 2, 0, [70, 9], [0, 1])
     _check(got, ref, "f32", f"H {H} F {F}")
+
+
+# One row of infinities, one of NaN at the ends of neighbouring groups, and an
+# expert of infinite weights: rows of every kernel and tile shape (decode
+# launches with one and two K parts, 64-, 128- and 256-row tiles, fp32 row
+# blocks) do not see their neighbours'.
+@pytest.mark.parametrize("dtype,F,rows", [("bf16", 384, 7), ("bf16", 8192, 13), ("bf16", 384, 30), ("bf16", 384, 90),
+                                          ("bf16", 8192, 90), ("bf16", 384, 200), ("f32", 384, 10), ("f32", 384, 90)])
+def test_nonfinite_rows_stay_alone(dtype, F, rows, device):
+    log(f"{dtype} F {F} rows {rows} infinities and NaN")
+    lens, experts = [rows, rows + 1, 2], [0, 1, 2]
+
+    def spoil(gu, dn, acts):
+        acts[0][-1] = float("inf")
+        acts[1][0] = float("nan")
+        gu[2], dn[2] = float("inf"), float("-inf")
+
+    (o, h, _), _ = _step(device, dtype, 256, F, 3, 0, lens, experts)
+    (o2, h2, _), _ = _step(device, dtype, 256, F, 3, 0, lens, experts, spoil=spoil)
+    bad = torch.zeros(sum(lens), dtype=torch.bool, device=device)
+    bad[rows - 1:rows + 1] = True
+    bad[-2:] = True
+    for got, ref in ((o2, o), (h2, h)):
+        assert torch.equal(got[~bad], ref[~bad])
+        assert not torch.isfinite(got[bad]).any()
+
+
+def test_f32_subnormal_operands(device):
+    """fp32 products with a subnormal operand, and subnormal sums: rows that see only
+    column 0 (gate) and a subnormal column 1 (up), down weights near the smallest normal."""
+    log("f32 subnormals")
+    H, F = 256, 128
+
+    def spoil(gu, dn, acts):
+        for a in acts:
+            a[:, 1] = 1e-41 * (1 + torch.arange(a.shape[0], device=device))
+            a[:, 2:] = 0
+        gu.zero_()
+        gu[:, :F, 0] = 0.5
+        gu[:, F:, 1] = 1e38
+        dn.mul_(1e-37)
+
+    got, ref = _step(device, "f32", H, F, 2, 0, [70, 9], [0, 1], spoil=spoil)
+    assert 0 < ref[0].abs().max() < 1e-38
+    # each of the sums' F terms and the sums themselves are rounded to multiples of 2^-149
+    assert (got[0].double() - ref[0]).abs().max() <= (F + 2) * 2.0 ** -149 + 1e-5 * ref[0].abs().max()
+    _check(got[1:], ref[1:], "f32", "subnormals")

@@ -26,6 +26,15 @@ SMALL += [mini(BY_NAME["qwen_moe_bf16"], E=64, D=16, H=256, F=128, T=96, L=3).sc
           mini(BY_NAME["dsv3_share_bf16"], E=128, D=64, H=256, F=128, T=96, L=3).scaled(name="d64_bf16")]
 SMALL_IDS += ["d16", "d64"]
 
+# decode passes: at most 32 tokens in all (the weight-streaming expert kernels,
+# one K part and two) whose grouped rows the grouping's launch copies (up to
+# 128 KB) or leaves to the gather
+SMALL += [mini(BY_NAME["qwen_moe_bf16"], H=256, T=2).scaled(name="decode_bf16"),
+          mini(BY_NAME["qwen_moe_bf16"], H=768, T=4).scaled(name="decode_gather_bf16"),
+          mini(BY_NAME["mixtral_bf16"], H=256, F=8192, T=3, L=2).scaled(name="decode_longk_bf16"),
+          CONFIGS[0].scaled(name="decode_f32", T=3)]
+SMALL_IDS += ["decode", "decode_gather", "decode_longk", "decode_f32"]
+
 
 def _compare(cfg, device, policies):
     inp = DeviceInputs(cfg, device)
