@@ -22,8 +22,6 @@
 //
 // Pair q = (tok_base[rho] + t) * (k+S) + r; key = layer*(E+S) + slot expert.
 // All results are integers fixed by the inputs (no order-dependent atomics).
-#include <type_traits>
-
 #include "eb_internal.h"
 #include "eb_numeric.h"
 
@@ -299,7 +297,6 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   __shared__ int running[kMaxKeys];                        // per-key totals, then offsets / cursors
   __shared__ unsigned long long masks[kSmallWords / 2];    // [pieces][E] lanes per expert, then the counts
   __shared__ int wtot[kScanWaves], s_layer[kSmallPieces];
-  __shared__ bool s_head[kSmallPieces], s_repeat;          // the piece starts a chunk; some token repeats a pick
   __shared__ int s_pos[kSmallRows];                        // inv of a step whose rows are copied here
   const RunTable& rt = rta.get();
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -321,14 +318,14 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   // this lane's token of piece p and its picks
   struct Token {
     int rho, q0, rows;     // entry, first pair, tokens of the piece
-    bool head;
+    int last;              // last piece of its chunk
     int e[kMaxSlots];
   } tk;
   auto load = [&](int p) {
     tk.rho = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < n && upto <= p)));
-    const int t0 = (p - __shfl(upto - own, tk.rho, kWave)) * kWave;
+    const int first = __shfl(upto - own, tk.rho, kWave), t0 = (p - first) * kWave;
     tk.rows = min(kWave, __shfl(len, tk.rho, kWave) - t0);
-    tk.head = t0 % kPermChunk == 0;
+    tk.last = min(first + ((p - first) | (kPermChunk / kWave - 1)), __shfl(upto, tk.rho, kWave) - 1);
     tk.q0 = (__shfl(tok0, tk.rho, kWave) + t0 + lane) * slots;
     const int32_t* ix = in_global(rt.idx[tk.rho]) + (size_t)(t0 + lane) * k;
 #pragma unroll
@@ -353,64 +350,57 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   if (wave < units) read_row(wave);
 
   if (tid < kWorkWords && tid != kWorkTiles && tid != kWorkTiles + 1) work_ctr[tid] = 0;
-  if (tid == 0) s_repeat = false;
   for (int i = tid; i < n_keys; i += kScanThreads) running[i] = 0;
   for (int i = tid; i < np * E; i += kScanThreads) masks[i] = 0ull;
   for (int i = tid; i < np * ES; i += kScanThreads) cnt[i] = 0;
   __syncthreads();
   for (int p = wave; p < np; p += kScanWaves) {
     if (p != p_last) load(p_last = p);
-    if (lane == 0) {
-      s_layer[p] = rt.layer[tk.rho];
-      s_head[p] = tk.head;
-    }
+    if (lane == 0) s_layer[p] = rt.layer[tk.rho];
     if (lane < S) cnt[p * ES + E + lane] = tk.rows;
 #pragma unroll
     for (int r = 0; r < kMaxSlots; ++r)
       if (r < k && lane < tk.rows) {
         atomicOr(&masks[p * E + tk.e[r]], 1ull << lane);
-        atomicAdd(&cnt[p * ES + tk.e[r]], 1);
+        // a repeated pick has no row of its own: it counts at the chunk's end
+        bool again = false;
+#pragma unroll
+        for (int i = 0; i < r; ++i) again |= tk.e[i] == tk.e[r];
+        atomicAdd(&cnt[(again ? tk.last : p) * ES + tk.e[r]], 1);
       }
   }
   __syncthreads();
   for (int i = tid; i < np * ES; i += kScanThreads) {
-    const int p = i / ES, c = i - p * ES;
+    const int p = i / ES;
     const int v = cnt[i];
-    if (v) atomicAdd(&running[s_layer[p] * ES + c], v);
-    if (v > 1 && c < E && __popcll(masks[p * E + c]) != v) s_repeat = true;
+    if (v) atomicAdd(&running[s_layer[p] * ES + i - p * ES], v);
   }
   __syncthreads();
   offsets_and_tiles(running, n_keys, wtot, offsets, tiles, bm, tail, max_tiles, work_ctr);
   // first position of every (piece, column): the pieces in order
-  auto first_positions = [&](auto repeats) {
-    for (int c = tid; c < ES; c += kScanThreads) {
-      int layer = -1, cur = 0, at = 0;
-      for (int p0 = 0; p0 < np; p0 += 8) {
-        int v[8], l[8];  // read ahead of the stores
+  for (int c = tid; c < ES; c += kScanThreads) {
+    int layer = -1, cur = 0;
+    for (int p0 = 0; p0 < np; p0 += 8) {
+      int v[8], l[8];  // read ahead of the stores
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (p0 + j < np) {
-            v[j] = cnt[(p0 + j) * ES + c];
-            l[j] = s_layer[p0 + j];
-          }
+      for (int j = 0; j < 8; ++j)
+        if (p0 + j < np) {
+          v[j] = cnt[(p0 + j) * ES + c];
+          l[j] = s_layer[p0 + j];
+        }
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (p0 + j < np) {
-            if (l[j] != layer) {
-              if (layer >= 0) running[layer * ES + c] = cur;
-              cur = running[l[j] * ES + c];
-              layer = l[j];
-            }
-            if (!repeats || s_head[p0 + j]) at = cur;
-            cnt[(p0 + j) * ES + c] = at;
-            if (repeats) at += c < E ? __popcll(masks[(p0 + j) * E + c]) : v[j];
-            cur += v[j];
+      for (int j = 0; j < 8; ++j)
+        if (p0 + j < np) {
+          if (l[j] != layer) {
+            if (layer >= 0) running[layer * ES + c] = cur;
+            cur = running[l[j] * ES + c];
+            layer = l[j];
           }
-      }
+          cnt[(p0 + j) * ES + c] = cur;
+          cur += v[j];
+        }
     }
-  };
-  if (s_repeat) first_positions(std::true_type{});
-  else first_positions(std::false_type{});
+  }
   __syncthreads();
   for (int p = p_last; p >= 0; p -= kScanWaves) {
     if (p != p_last) load(p);
