@@ -11,7 +11,7 @@
 //                        it also clears the work counters of the step's
 //                        grouped GEMM launches
 //                        (the three above and perm_scatter_kernel: one launch,
-//                        perm_small_kernel, for steps of up to about 1000 tokens,
+//                        perm_small_kernel, for steps of up to 1000 to 2000 tokens,
 //                        with the gather's copies for those of a few)
 //   perm_scatter_kernel  per chunk: stable rank of each pair inside its key from
 //                        per-wavefront 64-bit expert masks (popcount of the lanes
@@ -273,10 +273,24 @@ __global__ __launch_bounds__(kPermChunk) void perm_scatter_kernel(
 // token that picks an expert more than once (a caller's picks may): such pairs
 // share the token's row, one for each token of a kPermChunk-token chunk, and
 // the next chunk starts after all the pairs counted.
-// It costs about 7 us plus 65 ns per slot of a piece (LDS atomics, then
-// scattered stores, all from one CU): 16 pieces of 8 slots over 64 experts 15
-// us against 17 (5 + 7 + 5) for the three launches, 32 pieces of 8 slots 24 us
-// against 20, 32 of 2 slots 16 us; hence the limits.
+// Bound by the latency of its phases, then by one CU's LDS atomics and
+// scattered stores; a wavefront takes a second piece from the 17th on.
+// Kernel times: 8 to 10 us up to 4 pieces, 11 at 8 pieces of 8 slots (over 64
+// experts) and 16 of 2, 16 at 16 of 8, 15 at 32 of 2; 20 at 16 of 8 over 256
+// experts.  What the three launches take depends on their chunks; per step of
+// a pass, one workgroup less three launches, in us:
+//   entries of 64 tokens (a chunk each): 20 pieces of 2 slots over 8 experts
+//     -3.0, of 4 over 256 -4.1, of 6 over 64 -1.4; 16 of 8 over 64 +0.9, over
+//     128 -0.6;
+//   entries of 128 tokens (two pieces a chunk): 16 pieces of 8 over 60 -2.3, over
+//     256 +2.3; 32 of 2 over 8 +0.2;
+//   entries of 256 tokens (four pieces a chunk): 16 pieces of 2 slots over 8
+//     experts -1.6, of 6 over 64 -1.4, of 4 over 256 -0.7, of 8 over 64 +1.0,
+//     of 8 over 256 +3.1; 12 of 8 over 256 -1.2; 28 of 2 over 8 +1.1, of 4
+//     over 256 +4.5.
+// Hence the limits (perm_small): with a chunk for every two pieces up to 32
+// pieces and 128 pieces x slots, fewer with many experts; else one piece per
+// wavefront and 128 pieces x (slots + experts / 96).
 constexpr int kSmallPieces = 32;      // pieces of a small step
 constexpr int kSmallSlots = 128;      // pieces x slots of a small step
 constexpr int kSmallWords = 23040;    // LDS words for the pieces' expert masks and counts (90 KB)
@@ -501,11 +515,16 @@ void perm_scatter_impl(RTA a, int grid_chunks, const int32_t* chunk_base, int32_
   prof_stop(EB_K_PERM_SCATTER, s);
 }
 
-// Whether a step of `pieces` 64-token pieces runs in perm_small_kernel: the
-// pieces' masks and counts fit its LDS, and there are few enough of them that
-// one workgroup is faster than three launches (measured there).
-bool perm_small(const eb_model_desc& d, int pieces) {
-  return pieces <= kSmallPieces && pieces * (d.k + d.S) <= kSmallSlots && pieces * (3 * d.E + d.S) <= kSmallWords;
+// Whether a step of `pieces` 64-token pieces and `chunks` chunks runs in
+// perm_small_kernel: the pieces' masks and counts fit its LDS, and there are
+// few enough of them that one workgroup is faster than three launches
+// (measured there).
+bool perm_small(const eb_model_desc& d, int pieces, int chunks) {
+  if (pieces > kSmallPieces || pieces * (3 * d.E + d.S) > kSmallWords) return false;
+  const int slots = d.k + d.S;
+  const int cost = pieces * (96 * slots + d.E);  // 96 experts count as a slot
+  if (2 * chunks >= pieces) return pieces * slots <= kSmallSlots && cost <= 96 * kSmallSlots + 2048;
+  return pieces <= kScanWaves && cost <= 96 * kSmallSlots;
 }
 
 template <class RTA>
@@ -538,7 +557,7 @@ void permute_impl(RTA a, const eb_model_desc& d, int grid_chunks, int grid_token
   const int bm = gemm_bm(d.dtype);
   const TailRule tail = gemm_tail(d.dtype, d.F);
   const int elem_bytes = d.dtype == EB_DTYPE_BF16 ? 2 : 4;
-  if (perm_small(d, pieces)) {
+  if (perm_small(d, pieces, grid_chunks)) {
     const bool copy = (long long)grid_tokens * (d.k + d.S) * d.H * elem_bytes <= kSmallCopy;
     perm_small_impl(a, b, bm, tail, copy ? d.H * elem_bytes : 0, s);
     if (copy) return;

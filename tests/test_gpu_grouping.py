@@ -1,6 +1,8 @@
 """A step's grouping (perm, inv, offsets, gathered rows) against the oracle's
 stable permutation, on both sides of the one-workgroup kernel's limits: 32
-pieces of up to 64 tokens, 128 pieces x slots, 23040 LDS words.  All integers and copies: exact."""
+pieces of up to 64 tokens, 128 pieces x slots, 23040 LDS words; where 256-token
+chunks hold more than two pieces on average, 16 pieces and 128 pieces x (slots +
+experts / 96), elsewhere 149 of these.  All integers and copies: exact."""
 import numpy as np
 import pytest
 import torch
@@ -24,6 +26,13 @@ CASES = {
     "64_entries": ("bf16", 5, 8, 0, 2, [1 + i % 7 for i in range(64)]),
     "32_pieces": ("bf16", 2, 16, 1, 3, [1024, 1, 64, 895]),
     "33_pieces": ("bf16", 2, 16, 1, 3, [1024, 1, 65, 895]),
+    "32_full_pieces": ("bf16", 2, 16, 1, 3, [64] * 32),
+    "16_in_chunks": ("bf16", 2, 16, 1, 3, [512, 1, 64, 320, 1]),
+    "17_in_chunks": ("bf16", 2, 16, 1, 3, [512, 1, 64, 321, 1]),
+    "cost_full": ("bf16", 2, 192, 0, 6, [1024]),                    # 16 x (6 + 2) = 128; 193 experts: over
+    "cost_over": ("bf16", 2, 193, 0, 6, [1024]),
+    "short_cost_full": ("bf16", 2, 128, 0, 8, [65] * 8),            # 16 x (8 + 4/3) = 149
+    "short_cost_over": ("bf16", 2, 129, 0, 8, [65] * 8),
     "slots_full": ("bf16", 3, 256, 0, 8, [65] * 8),
     "slots_over": ("bf16", 3, 256, 1, 8, [65] * 8),
     "lds_full": ("bf16", 3, 256, 0, 1, [64] * 30),
