@@ -68,7 +68,8 @@ constexpr int kXcds = 8;
 // memory-side cache alone, and HBM delivers 6.2 instead of 5.5 TB/s (64 tokens
 // on 8 experts of H = 4096, F = 14336: step 495 -> 454 us).
 constexpr int kNonTemporal = 2;  // bit nt of a buffer load's cache policy
-// Most tokens at one layer for which a launch counts as such.  In steps of
+// Most tokens at one layer (GroupedProblem::layer_tokens, a bound) for which a
+// launch counts as such.  In steps of
 // three micro-batches at three layers, 60 + 4 experts, H = 2048, F = 1408, nt
 // loads for items of up to 64 rows take 4 to 5% off at 64 and 96 tokens,
 // nothing at 128, and add 1 to 3% from 192 on; for longer items they gain
@@ -536,9 +537,9 @@ __device__ __forceinline__ void run_item(const GroupedProblem& p, bf16_t* smem, 
 
   // 32-row blocks of this wave's TM rows that hold rows of the group
   const int nact = min(tm / 32, max(0, (row_end - (row0 + wm * tm) + 31) / 32));
-  // bf16 outputs use the transposed accumulators (one 8-byte store per four
-  // consecutive columns); fp32 partial sums the row layout (32 lanes store a
-  // whole 128-byte line)
+  // bf16 outputs use the transposed accumulators (a lane holds four consecutive
+  // columns, one 8-byte LDS write of epilogue_tr); fp32 partial sums the row
+  // layout (32 lanes store a whole 128-byte line)
   if (MODE == MODE_GATEUP || part == nullptr) {
     k_loop_nact<C, true>(kl, acc, nact);
     bar_lds();  // every wave is done with the ring before it is written again
@@ -610,8 +611,9 @@ __device__ __forceinline__ Tile2 item_tile(int local, int mt, int n_ntiles) {
 // One thread's view of the item counters: the XCD whose range it draws from.
 // Each XCD's counter has a cache line of its own, and another XCD's counter is
 // read before it is drawn from: when every workgroup drew from all eight in
-// one line on its way out, those 2000 atomics ran one after the other for
-// about 20 us at the end of each launch.
+// one line on its way out, those 2000 atomics ran one after the other (66 + 8
+// experts of H = 2048, F = 1408: gate/up of one token 37 -> 23 us, of 96 tokens
+// on three layers 172 -> 165, of 3072 tokens on five 768 -> 764).
 //
 // The list's last n_tiles[0] - n_tiles[1] row blocks are small ones the scan
 // set aside: their items are taken once the others are gone, so that the
@@ -793,8 +795,8 @@ __global__ __launch_bounds__(64, 1) void stream_gemm_bf16(GroupedProblem p, Weig
 
   // Units: XCD x owns a contiguous eighth of the list and its wavefronts take
   // every per_xcd-th unit of it.  Units all cost the same, so a counter would
-  // balance nothing, and a thousand wavefronts drawing from counters in one
-  // cache line took 60 us.
+  // balance nothing (counters were measured only with all of them in one cache
+  // line, which took a thousand wavefronts 60 us).
   const long long total = (long long)(*p.n_tiles) * nsub;
   const int xcd = blockIdx.x % kXcds, per_xcd = gridDim.x / kXcds;
   const int u_end = (int)(((xcd + 1) * total) / kXcds);
@@ -1230,8 +1232,8 @@ static int persistent_grid() {
 }
 
 // Whether a launch's groups are so small that it only streams weights: at
-// most 32 tokens at any layer (one MFMA block of rows), and K long enough for
-// the streams' look-ahead.  Up to 64 tokens (two blocks, 16 KB ring slots) the
+// most 32 tokens at any layer by the bound the host has (one MFMA block of
+// rows), and K long enough for the streams' look-ahead.  Up to 64 tokens (two blocks, 16 KB ring slots) the
 // 256-column items measured the same or faster.
 static bool stream_launch(const GroupedProblem& p) {
   return p.layer_tokens <= 32 && p.H / BK >= kStreamMinStages && p.F / BK / p.ksplit >= kStreamMinStages;
