@@ -635,12 +635,18 @@ struct ItemQueue {
   int32_t* ctr;
   long long main;  // items before the ones set aside
   int total, xcd, victim, per_xcd;  // victim: XCD range drawn from, + kXcds for its set-aside range
+  // Every item has a workgroup by number, nothing is drawn: the counters are
+  // neither drawn from nor read (15 reads in turn on each workgroup's way out:
+  // fp32 down launch of 774 tokens on three layers of 8 experts, H = 256,
+  // F = 128, 14.2 -> 8.2 us).
+  bool numbered;
   __device__ __forceinline__ ItemQueue(const GroupedProblem& p, int nsub)
       : ctr(p.work_ctr), total(p.n_tiles[0] * nsub), xcd(blockIdx.x % kXcds), victim(blockIdx.x % kXcds),
         per_xcd(gridDim.x / kXcds) {
     const int last = total % (int)gridDim.x;  // items of the last, partial round
     const bool aside = p.ksplit == 1 || total <= (int)gridDim.x || (last > 0 && 2 * last <= (int)gridDim.x);
     main = aside ? (long long)p.n_tiles[1] * nsub : total;
+    numbered = main == total && total <= kXcds * per_xcd;
   }
   __device__ __forceinline__ int bound(int x) const {  // first item of range x; bound(2 kXcds) = total
     return x < kXcds ? (int)((x * main) / kXcds) : (int)(main + ((x - kXcds) * (total - main)) / kXcds);
@@ -648,7 +654,7 @@ struct ItemQueue {
   __device__ __forceinline__ int32_t* counter() const {
     return ctr + (victim < kXcds ? victim * kWorkStride : (victim - kXcds) * kWorkStride + kWorkTail);
   }
-  __device__ __forceinline__ int draw() const { return atomicAdd(counter(), 1); }
+  __device__ __forceinline__ int draw() const { return numbered ? 0 : atomicAdd(counter(), 1); }
   // The first items of an XCD's range go to its workgroups by number (drawn,
   // the first few to start would each hold a second item while others have
   // none), the rest through its counter.
@@ -656,6 +662,7 @@ struct ItemQueue {
   // item index from a value drawn from victim's counter, or -1 once everything
   // is taken: the own range, the other XCDs', then the set-aside ones alike
   __device__ __forceinline__ int settle(int got) {
+    if (numbered) return -1;
     int it = drawn(got);
     while (it >= bound(victim + 1)) {
       if (victim < kXcds) {

@@ -164,6 +164,16 @@ def test_f32_shapes(H, F, device):
     _check(got, ref, "f32", f"H {H} F {F}")
 
 
+# Launches of as many items as workgroups (256 of bf16, 512 of fp32: every item
+# has a workgroup by number, none is drawn), fewer and more
+@pytest.mark.parametrize("dtype,rows", [("bf16", 257), ("bf16", 65536), ("bf16", 65537), ("f32", 65), ("f32", 16384),
+                                        ("f32", 16385)])
+def test_items_by_number(dtype, rows, device):
+    log(f"{dtype} {rows} rows of one expert")
+    got, ref = _step(device, dtype, 256, 128, 1, 0, [rows], [0])
+    _check(got, ref, dtype, f"{rows} rows")
+
+
 # One row of infinities, one of NaN at the ends of neighbouring groups, and an
 # expert of infinite weights: rows of every kernel and tile shape (decode
 # launches with one and two K parts, 64-, 128- and 256-row tiles, fp32 row
