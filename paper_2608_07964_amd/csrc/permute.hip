@@ -317,6 +317,8 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int E = rt.E, S = rt.S, k = rt.k, n = rt.n, ES = E + S, slots = k + S, n_keys = rt.L * ES;
 
+  // value of a uniform lane, in a scalar register (a shuffle goes through LDS)
+  auto lane_of = [](int v, int from) { return __builtin_amdgcn_readlane(v, from); };
   // lane i: entry i's first piece (pieces of an entry in token order, entries in order)
   const int tok0 = lane < n ? rt.tok_base[lane] : 0, len = lane < n ? rt.tok_base[lane + 1] - tok0 : 0;
   int upto = (len + kWave - 1) / kWave;
@@ -326,7 +328,7 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
     const int y = __shfl_up(upto, off, kWave);
     if (lane >= off) upto += y;
   }
-  const int np = min(__shfl(upto, kWave - 1, kWave), kSmallPieces);
+  const int np = min(lane_of(upto, kWave - 1), kSmallPieces);
   int* cnt = reinterpret_cast<int*>(masks + np * E);       // [pieces][ES] counts, then first positions
 
   // this lane's token of piece p and its picks
@@ -337,10 +339,10 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   } tk;
   auto load = [&](int p) {
     tk.rho = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < n && upto <= p)));
-    const int first = __shfl(upto - own, tk.rho, kWave), t0 = (p - first) * kWave;
-    tk.rows = min(kWave, __shfl(len, tk.rho, kWave) - t0);
-    tk.last = min(first + ((p - first) | (kPermChunk / kWave - 1)), __shfl(upto, tk.rho, kWave) - 1);
-    tk.q0 = (__shfl(tok0, tk.rho, kWave) + t0 + lane) * slots;
+    const int last = lane_of(upto, tk.rho), first = last - lane_of(own, tk.rho), t0 = (p - first) * kWave;
+    tk.rows = min(kWave, lane_of(len, tk.rho) - t0);
+    tk.last = min(first + ((p - first) | (kPermChunk / kWave - 1)), last - 1);
+    tk.q0 = (lane_of(tok0, tk.rho) + t0 + lane) * slots;
     const int32_t* ix = in_global(rt.idx[tk.rho]) + (size_t)(t0 + lane) * k;
 #pragma unroll
     for (int r = 0; r < kMaxSlots; ++r)
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(kScanThreads) void perm_small_kernel(
   auto read_row = [&](int u) {
     const int g = u / row_pieces, at = (u - g * row_pieces) * kSmallRowPiece + lane * 16;
     const int rho = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < n && tok0 + len <= g)));
-    const int t = g - __shfl(tok0, rho, kWave);
+    const int t = g - lane_of(tok0, rho);
     const uint8_t* src = in_global(static_cast<const uint8_t*>(rt.a[rho])) + (size_t)t * row_bytes;
     if (at < row_bytes) row = *reinterpret_cast<const uint4*>(src + at);
   };
