@@ -611,9 +611,9 @@ __device__ __forceinline__ Tile2 item_tile(int local, int mt, int n_ntiles) {
 // One thread's view of the item counters: the XCD whose range it draws from.
 // Each XCD's counter has a cache line of its own, and another XCD's counter is
 // read before it is drawn from: when every workgroup drew from all eight in
-// one line on its way out, those 2000 atomics ran one after the other (66 + 8
-// experts of H = 2048, F = 1408: gate/up of one token 37 -> 23 us, of 96 tokens
-// on three layers 172 -> 165, of 3072 tokens on five 768 -> 764).
+// one line on its way out, those 2000 atomics ran one after the other (gate/up
+// at H = 2048, F = 1408: one token on 64 + 2 experts 37 -> 23 us, 80 tokens on
+// three layers of 60 + 4 172 -> 165, 3072 tokens on five of 64 + 2 768 -> 764).
 //
 // The list's last n_tiles[0] - n_tiles[1] row blocks are small ones the scan
 // set aside: their items are taken once the others are gone, so that the
